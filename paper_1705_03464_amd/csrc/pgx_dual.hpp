@@ -432,50 +432,6 @@ static __global__ void k_dual_pair_grad(const int32_t* __restrict__ key, int64_t
   acc[p] = (float)s;
 }
 
-// The points whose CIC footprint reaches line (y, z): those of the four base
-// lines (y, z), (y-1, z), (y, z-1), (y-1, z-1), taken as one index range
-// (range q = base line q, whose y / z weight is the upper one when bit 0 /
-// bit 1 of q is set).
-struct LineRanges {
-  int o1, o2, o3, n, d0, d1, d2, d3;
-  template <typename T>
-  __device__ __forceinline__ void init(const PointSet<T>& ps, int y, int z, int N) {
-    const int ym = (y - 1) & (N - 1), zm = (z - 1) & (N - 1);
-    const int k0 = z * N + y, k1 = z * N + ym, k2 = zm * N + y, k3 = zm * N + ym;
-    const int s0 = ps.line_start[k0], e0 = ps.line_start[k0 + 1];
-    const int s1 = ps.line_start[k1], e1 = ps.line_start[k1 + 1];
-    const int s2 = ps.line_start[k2], e2 = ps.line_start[k2 + 1];
-    const int s3 = ps.line_start[k3], e3 = ps.line_start[k3 + 1];
-    o1 = e0 - s0;
-    o2 = o1 + (e1 - s1);
-    o3 = o2 + (e2 - s2);
-    n = o3 + (e3 - s3);
-    d0 = s0;
-    d1 = s1 - o1;
-    d2 = s2 - o2;
-    d3 = s3 - o3;
-  }
-  // range and point of combined index i < n
-  __device__ __forceinline__ int range(int i) const { return (i >= o1) + (i >= o2) + (i >= o3); }
-  __device__ __forceinline__ int point(int i, int q) const {
-    return i + (q == 0 ? d0 : q == 1 ? d1 : q == 2 ? d2 : d3);
-  }
-};
-
-// CIC weights of point p on a line of its range q: the two x nodes
-// (x0, x0 + 1) get w * (1 - fx) and w * fx, w = weight * y weight * z weight.
-template <typename T>
-__device__ __forceinline__ void cic_on_line(const PointSet<T>& ps, int p, int q, T& wa, T& wb,
-                                            int& x0) {
-  const T fy = ps.fy[p], fz = ps.fz[p], fx = ps.fx[p];
-  const T wy = (q & 1) ? fy : (T)1 - fy;
-  const T wz = (q & 2) ? fz : (T)1 - fz;
-  const T w = (ps.wt ? ps.wt[p] : (T)1) * wy * wz;
-  wa = w * ((T)1 - fx);
-  wb = w * fx;
-  x0 = ps.x0[p];
-}
-
 // Segmented inclusive sums over one wavefront (64 lanes, lane = threadIdx.x
 // mod 64) whose keys ascend, so that equal keys form contiguous runs: after
 // add(v), each lane holds the sum of v over the lanes of its run up to and
@@ -527,131 +483,175 @@ struct WaveRuns {
   }
 };
 
-// x pass of the Pi fields with the CIC scatter fused in.  Block = W lines
-// (y, z), each for every slot of the batch in turn (bins 2(q0+slot),
-// 2(q0+slot)+1): the line is built in LDS from the points whose CIC
-// footprint reaches it, each weighted by its pair weight and its field's
-// coefficient pair, transformed along x and written.  The first point of
-// every thread (most lines have at most TPL points) stays in registers
-// across the slots, with its coefficients for the next slot loaded one slot
-// ahead; further points of crowded lines are read again per slot.  Every one
-// of the N*N lines is written (zero lines transform to zero).  With HARM
-// (the multipoles' adjoint) the slots hold (bin, harmonic) combos c = b nh + h
-// and each pair's coefficient is also multiplied by its harmonic
+template <typename T>
+__device__ __forceinline__ T pick3(const T* w, int j) {
+  return j == 0 ? w[0] : (j == 1 ? w[1] : w[2]);
+}
+
+// x pass of the Pi fields with the scatter fused in.  Block = W neighbouring
+// lines (y, z), each for every slot of the batch in turn (bins 2(q0+slot),
+// 2(q0+slot)+1): the lines are built in LDS from the points whose footprint
+// reaches them, each weighted by its pair weight and its field's coefficient
+// pair, transformed along x and written.  Every one of the N*N lines is
+// written (zero lines transform to zero).
+//
+// Sources of a line: its CIC base lines (y, z), (y-1, z), (y, z-1),
+// (y-1, z-1) (range q: the y / z weight is the upper one when bit 0 / bit 1
+// of q is set); in a TSC plan, whose catalogue is keyed by the nearest node,
+// the nine lines (y + q % 3 - 1, z + q / 3 - 1), and three x nodes per point.
+// With HARM (the multipoles' adjoint) the slots hold (bin, harmonic) combos
+// c = b nh + h and each pair's coefficient is also multiplied by its harmonic
 // yl[h P + p] (line-major pair index p).
-template <typename T, typename Sh, int W, bool HARM = false>
+//
+// What bounds it: the points of the few crowded lines of a clustered
+// catalogue, a chain of loads and LDS atomics, not the dense output.  So all
+// points of the block's lines form one index range that all its threads walk
+// together (BlockRanges), whatever line they belong to: with TPL threads per
+// line a 256^3 grid left a crowded line to 32 threads.  Contributions of
+// points on the same x node are summed across the wavefront first (the points
+// of a source line run in x order), and only the last lane of each run adds
+// to LDS.  The first KEEP points of every thread stay in registers across
+// the slots, their coefficients loaded one slot ahead; further points are
+// read again per slot, the next trip's in flight during the current one.
+template <typename T, typename Sh, int W, bool TSC = false, bool HARM = false>
 static __global__ void __launch_bounds__(W * Sh::TPL)
 k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2* __restrict__ coef,
                 int F, int q0, int nq, C<T>* __restrict__ out, int64_t out_slot,
                 const C<T>* __restrict__ tw_g, const float* __restrict__ yl = nullptr, int nh = 1,
                 int64_t P = 0) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int NT = W * TPL, NB = TSC ? 9 : 4, NX = TSC ? 3 : 2, NR = W * NB, KEEP = 2;
+  static_assert(N % W == 0, "the lines of a block share their z row");
   __shared__ C<T> tw_s[Sh::tw_entries()];
-  __shared__ C<T> lines[W][LL];
+  __shared__ C<T> lines[W * LL];
+  __shared__ BlockRanges<NR, NT> br;
   load_twiddles<T, Sh>(tw_s, tw_g);
-  const int t = threadIdx.x % TPL, l = threadIdx.x / TPL;
+  const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
   const int li = blockIdx.x * W + l;  // < N*N by the grid
-  const int y = li % N, z = li / N;
-  C<T>* line = lines[l];
-  LineRanges lr;
-  lr.init(ps, y, z, N);
-  const bool has0 = t < lr.n;
-  T wa0 = (T)0, wb0 = (T)0;
-  int xa0 = 0, f0 = 0, p0 = 0;
-  if (has0) {
-    const int q = lr.range(t), p = lr.point(t, q);
-    cic_on_line(ps, p, q, wa0, wb0, xa0);
-    f0 = lfield[p];
-    p0 = p;
-  }
-  // the pair's harmonic factors of the slot's two combos (multipoles)
-  auto harm = [&](float2 c, int p, int slot) {
-    if constexpr (HARM) {
-      const int c1 = 2 * (q0 + slot);
-      c.x *= yl[(int64_t)(c1 % nh) * P + p];
-      c.y *= yl[(int64_t)((c1 + 1) % nh) * P + p];
-    }
-    return c;
-  };
-  const int xb0 = (xa0 + 1) & (N - 1);
-  // one line per wavefront: contributions of points on the same x node are
-  // summed across the wavefront first (the points of a base line run in x
-  // order), and only the last lane of each run adds to LDS
-  constexpr bool RUNS = TPL == 64 && std::is_same<T, float>::value;
-  WaveRuns r0;
-  if constexpr (RUNS) r0.init(has0 ? lr.range(t) * N + xa0 : 4 * N + t);
-  float2 cn = has0 ? coef[(int64_t)q0 * F + f0] : float2{0.f, 0.f};
-  for (int slot = 0; slot < nq; ++slot) {
-    const float2 c0 = has0 ? harm(cn, p0, slot) : cn;
-    if (has0 && slot + 1 < nq) cn = coef[(int64_t)(q0 + slot + 1) * F + f0];
-    if (slot > 0) block_sync();  // the previous slot's transform has left the LDS line
+  const int y_base = (int)(blockIdx.x * W) % N, z = (int)(blockIdx.x * W) / N;
+  C<T>* line = lines + l * LL;
 #pragma unroll
-    for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
-    block_sync();
+  for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
+  const int total = br.build([&](int r, int& s, int& e) {
+    const int q = r % NB, y = y_base + r / NB;
+    const int by = (TSC ? y + q % 3 - 1 : y - (q & 1)) & (N - 1);
+    const int bz = (TSC ? z + q / 3 - 1 : z - (q >> 1)) & (N - 1);
+    const int k = bz * N + by;
+    s = ps.line_start[k];
+    e = ps.line_start[k + 1];
+  });
+  struct Point {
+    T w[NX];     // weights of its x nodes on its line
+    int at[NX];  // their LDS entries
+    int key;     // (range, x node), ascending along the combined range
+    int f, p;
+    bool on;
+  };
+  auto fetch = [&](int i) {
+    Point a;
+    a.on = i < total;
+    a.key = NR * N + tid;  // idle lanes: past every real key, each its own
+    a.f = 0;
+    a.p = 0;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      a.w[j] = (T)0;
+      a.at[j] = 0;
+    }
+    if (a.on) {
+      const int r = br.find(i), q = r % NB, p = i + br.first[r], base = (r / NB) * LL;
+      const T fx = ps.fx[p], fy = ps.fy[p], fz = ps.fz[p];
+      const int x0 = ps.x0[p];
+      const T wt = ps.wt ? ps.wt[p] : (T)1;
+      a.f = lfield[p];
+      a.p = p;
+      if constexpr (TSC) {
+        T wx[3], wy[3], wz[3];
+        int lx;
+        tsc_weights3<T>(fy, wy);
+        tsc_weights3<T>(fz, wz);
+        // this line is node 1 - (q % 3) from the nearest node in y (range
+        // q % 3 = 0 holds points whose nearest line is y - 1), likewise in z
+        const T wyz = wt * pick3(wy, 2 - q % 3) * pick3(wz, 2 - q / 3);
+        tsc_axis<T>(x0, fx, lx, wx);
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+          a.w[j] = wyz * wx[j];
+          a.at[j] = base + lpad((lx + j) & (N - 1));
+        }
+        a.key = r * N + ((lx + 1) & (N - 1));
+      } else {
+        const T w = wt * ((q & 1) ? fy : (T)1 - fy) * ((q & 2) ? fz : (T)1 - fz);
+        a.w[0] = w * ((T)1 - fx);
+        a.w[1] = w * fx;
+        a.at[0] = base + lpad(x0);
+        a.at[1] = base + lpad((x0 + 1) & (N - 1));
+        a.key = r * N + x0;
+      }
+    }
+    return a;
+  };
+  // a wavefront's points into the lines: run sums, then the run's last lane
+  auto add = [&](const Point& a, const WaveRuns& r, float2 c, int slot) {
+    if constexpr (HARM) {
+      if (a.on) {
+        const int c1 = 2 * (q0 + slot);
+        c.x *= yl[(int64_t)(c1 % nh) * P + a.p];
+        c.y *= yl[(int64_t)((c1 + 1) % nh) * P + a.p];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      const T sx = r.add(a.w[j] * (T)c.x), sy = r.add(a.w[j] * (T)c.y);
+      if (a.on && r.tail) {
+        atomicAdd(&lines[a.at[j]].x, sx);
+        atomicAdd(&lines[a.at[j]].y, sy);
+      }
+    }
+  };
+  Point kept[KEEP];
+  WaveRuns runs[KEEP];
+  float2 cn[KEEP];
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) {
+    kept[k] = fetch(tid + k * NT);
+    runs[k].init(kept[k].key);
+    cn[k] = kept[k].on ? coef[(int64_t)q0 * F + kept[k].f] : float2{0.f, 0.f};
+  }
+  for (int slot = 0; slot < nq; ++slot) {
     const float2* cq = coef + (int64_t)(q0 + slot) * F;
-    if constexpr (RUNS) {
-      const T ax = r0.add(wa0 * (T)c0.x), ay = r0.add(wa0 * (T)c0.y);
-      const T bx = r0.add(wb0 * (T)c0.x), by = r0.add(wb0 * (T)c0.y);
-      if (has0 && r0.tail) {
-        atomicAdd(&line[lpad(xa0)].x, ax);
-        atomicAdd(&line[lpad(xa0)].y, ay);
-        atomicAdd(&line[lpad(xb0)].x, bx);
-        atomicAdd(&line[lpad(xb0)].y, by);
-      }
-      // crowded lines: further points, a wavefront-wide pass at a time
-      for (int base = TPL; base < lr.n; base += TPL) {
-        const int i = base + t;
-        const bool act = i < lr.n;
-        T wa = (T)0, wb = (T)0;
-        int xa = 0, q = 0;
-        float2 c = float2{0.f, 0.f};
-        if (act) {
-          q = lr.range(i);
-          const int p = lr.point(i, q);
-          cic_on_line(ps, p, q, wa, wb, xa);
-          c = harm(cq[lfield[p]], p, slot);
-        }
+    block_sync();  // the lines are zero
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+      if (k * NT >= total) break;
+      const float2 c = cn[k];
+      if (kept[k].on && slot + 1 < nq) cn[k] = cq[F + kept[k].f];
+      add(kept[k], runs[k], c, slot);
+    }
+    if (KEEP * NT < total) {
+      Point a = fetch(KEEP * NT + tid);
+      for (int base = KEEP * NT; base < total; base += NT) {
+        const float2 c = a.on ? cq[a.f] : float2{0.f, 0.f};
+        const Point nx = fetch(base + NT + tid);
         WaveRuns r;
-        r.init(act ? q * N + xa : 4 * N + t);
-        const T sx = r.add(wa * (T)c.x), sy = r.add(wa * (T)c.y);
-        const T tx = r.add(wb * (T)c.x), ty = r.add(wb * (T)c.y);
-        if (act && r.tail) {
-          const int xb = (xa + 1) & (N - 1);
-          atomicAdd(&line[lpad(xa)].x, sx);
-          atomicAdd(&line[lpad(xa)].y, sy);
-          atomicAdd(&line[lpad(xb)].x, tx);
-          atomicAdd(&line[lpad(xb)].y, ty);
-        }
-      }
-    } else {
-      if (has0) {
-        atomicAdd(&line[lpad(xa0)].x, wa0 * (T)c0.x);
-        atomicAdd(&line[lpad(xa0)].y, wa0 * (T)c0.y);
-        atomicAdd(&line[lpad(xb0)].x, wb0 * (T)c0.x);
-        atomicAdd(&line[lpad(xb0)].y, wb0 * (T)c0.y);
-      }
-      for (int i = t + TPL; i < lr.n; i += TPL) {
-        const int q = lr.range(i), p = lr.point(i, q);
-        T wa, wb;
-        int xa;
-        cic_on_line(ps, p, q, wa, wb, xa);
-        const float2 c = harm(cq[lfield[p]], p, slot);
-        const int xb = (xa + 1) & (N - 1);
-        atomicAdd(&line[lpad(xa)].x, wa * (T)c.x);
-        atomicAdd(&line[lpad(xa)].y, wa * (T)c.y);
-        atomicAdd(&line[lpad(xb)].x, wb * (T)c.x);
-        atomicAdd(&line[lpad(xb)].y, wb * (T)c.y);
+        r.init(a.key);
+        add(a, r, c, slot);
+        a = nx;
       }
     }
     block_sync();
+    // each line belongs to one wavefront from here to the next slot's scatter
     C<T> v[E];
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = line[lpad(t + TPL * m)];
-    block_sync();
+    wave_sync();
     line_fft<Sh, -1>(v, t, line, tw_s, wave_sync);
     C<T>* o = out + (int64_t)slot * out_slot + (int64_t)li * N;
 #pragma unroll
     for (int m = 0; m < E; ++m) o[t + TPL * m] = v[m];
+    wave_sync();
+#pragma unroll
+    for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
   }
 }
 
@@ -765,160 +765,6 @@ k_zdual_acc(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
     C<T>* p = acc_out + col + (int64_t)(t + TPL * m) * NN;
     const C<T> o = *p;
     *p = C<T>{o.x + acc[m].x, o.y + acc[m].y};
-  }
-}
-
-// The points whose TSC footprint reaches line (y, z) in a TSC plan's
-// line-major catalogue (keyed by nearest-node line): those of the nine lines
-// (y + dy, z + dz), dy, dz in {-1, 0, 1}, taken as one index range (range
-// q = 3 (dz + 1) + dy + 1).
-struct LineRanges9 {
-  int o[9], d[9], n;
-  // UNIFORM: the line is the same on every lane of the wavefront (one line
-  // per wavefront), so the table is taken into scalar registers
-  template <bool UNIFORM, typename T>
-  __device__ __forceinline__ void init(const PointSet<T>& ps, int y, int z, int N) {
-    n = 0;
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-      const int yy = (y + q % 3 - 1) & (N - 1), zz = (z + q / 3 - 1) & (N - 1);
-      const int k = zz * N + yy;
-      int s = ps.line_start[k], e = ps.line_start[k + 1];
-      if constexpr (UNIFORM) {
-        s = __builtin_amdgcn_readfirstlane(s);
-        e = __builtin_amdgcn_readfirstlane(e);
-      }
-      o[q] = n;
-      d[q] = s - n;
-      n += e - s;
-    }
-  }
-  __device__ __forceinline__ int range(int i) const {
-    int q = 0;
-#pragma unroll
-    for (int k = 1; k < 9; ++k) q += i >= o[k] ? 1 : 0;
-    return q;
-  }
-  // (selects, not indexing: the tables stay in registers)
-  __device__ __forceinline__ int point(int i, int q) const {
-    int dq = d[0];
-#pragma unroll
-    for (int k = 1; k < 9; ++k) dq = q == k ? d[k] : dq;
-    return i + dq;
-  }
-};
-template <typename T>
-__device__ __forceinline__ T pick3(const T* w, int j) {
-  return j == 0 ? w[0] : (j == 1 ? w[1] : w[2]);
-}
-
-// Pi scatter of the dual form's adjoint with TSC (the TSC form of
-// k_xscatter_dual): every pair whose footprint reaches line (y, z) adds
-// coef[slot][f] times its weight and its TSC weights along y, z (node offset
-// from its nearest node: the range it came from) and x (three nodes) to the
-// line in LDS; then the line is transformed along x and stored.  One line
-// per wavefront at 512^3: runs of equal (range, nearest x node) are summed
-// across the wavefront first (the catalogue is sorted that way within each
-// line), and only the last lane of a run issues the LDS atomics.
-template <typename T, typename Sh, int W>
-static __global__ void __launch_bounds__(W * Sh::TPL)
-k_xscatter_dual_tsc(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2* __restrict__ coef,
-                    int F, int q0, int nq, C<T>* __restrict__ out, int64_t out_slot,
-                    const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr bool RUNS = TPL == 64 && std::is_same<T, float>::value;
-  __shared__ C<T> tw_s[Sh::tw_entries()];
-  __shared__ C<T> lines[W][LL];
-  load_twiddles<T, Sh>(tw_s, tw_g);
-  const int t = threadIdx.x % TPL, l = threadIdx.x / TPL;
-  const int li = blockIdx.x * W + l;  // < N*N by the grid
-  const int y = li % N, z = li / N;
-  C<T>* line = lines[l];
-  LineRanges9 lr;
-  lr.template init<TPL == 64>(ps, y, z, N);
-  // point i of the line's nine ranges: TSC weights of this line (its weight
-  // times the y and z weights of the node offset its range stands for, times
-  // the three x weights), first x node and field
-  auto point_data = [&](int i, T* w, int& lx, int& q, int& f) {
-    q = lr.range(i);
-    const int p = lr.point(i, q);
-    T wy[3], wz[3];
-    tsc_weights3<T>(ps.fy[p], wy);
-    tsc_weights3<T>(ps.fz[p], wz);
-    // this line is node 1 - (q % 3) from the nearest node in y (range
-    // q % 3 = 0 holds points whose nearest line is y - 1), likewise in z
-    const T wyz = (ps.wt ? ps.wt[p] : (T)1) * pick3(wy, 2 - q % 3) * pick3(wz, 2 - q / 3);
-    T wx[3];
-    tsc_axis<T>(ps.x0[p], ps.fx[p], lx, wx);
-    w[0] = wyz * wx[0];
-    w[1] = wyz * wx[1];
-    w[2] = wyz * wx[2];
-    f = lfield[p];
-  };
-  // one trip of TPL points into the line: wavefront run sums over equal
-  // (range, nearest x node), then the run's last lane adds to LDS
-  auto add_trip = [&](bool act, const T* w, int lx, int q, float2 c) {
-    T sx[3], sy[3];
-    bool issue = act;
-    if constexpr (RUNS) {
-      WaveRuns r;
-      r.init(act ? q * N + ((lx + 1) & (N - 1)) : 9 * N + t);
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        sx[j] = r.add(w[j] * (T)c.x);
-        sy[j] = r.add(w[j] * (T)c.y);
-      }
-      issue = act && r.tail;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        sx[j] = w[j] * (T)c.x;
-        sy[j] = w[j] * (T)c.y;
-      }
-    }
-    if (issue) {
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        C<T>* a = &line[lpad((lx + j) & (N - 1))];
-        atomicAdd(&a->x, sx[j]);
-        atomicAdd(&a->y, sy[j]);
-      }
-    }
-  };
-  // the first two trips' point data stay in registers across the slots (most
-  // lines have at most 2 TPL points in their nine ranges); only the field's
-  // coefficients are read per slot
-  T w0[3] = {(T)0, (T)0, (T)0}, w1[3] = {(T)0, (T)0, (T)0};
-  int lx0 = 0, q0r = 0, f0 = 0, lx1 = 0, q1r = 0, f1 = 0;
-  const bool a0 = t < lr.n, a1 = TPL + t < lr.n;
-  if (a0) point_data(t, w0, lx0, q0r, f0);
-  if (a1) point_data(TPL + t, w1, lx1, q1r, f1);
-  for (int slot = 0; slot < nq; ++slot) {
-    if (slot > 0) block_sync();  // the previous slot's transform has left the LDS line
-#pragma unroll
-    for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
-    block_sync();
-    const float2* cq = coef + (int64_t)(q0 + slot) * F;
-    // every lane of a wavefront takes the same trips (RUNS: one line per wavefront)
-    if (lr.n > 0) add_trip(a0, w0, lx0, q0r, a0 ? cq[f0] : float2{0.f, 0.f});
-    if (lr.n > TPL) add_trip(a1, w1, lx1, q1r, a1 ? cq[f1] : float2{0.f, 0.f});
-    for (int base = 2 * TPL; base < lr.n; base += TPL) {
-      const int i = base + t;
-      const bool act = i < lr.n;
-      T w[3] = {(T)0, (T)0, (T)0};
-      int lx = 0, q = 0, f = 0;
-      if (act) point_data(i, w, lx, q, f);
-      add_trip(act, w, lx, q, act ? cq[f] : float2{0.f, 0.f});
-    }
-    block_sync();
-    C<T> v[E];
-#pragma unroll
-    for (int m = 0; m < E; ++m) v[m] = line[lpad(t + TPL * m)];
-    block_sync();
-    line_fft<Sh, -1>(v, t, line, tw_s, wave_sync);
-    C<T>* o = out + (int64_t)slot * out_slot + (int64_t)li * N;
-#pragma unroll
-    for (int m = 0; m < E; ++m) o[t + TPL * m] = v[m];
   }
 }
 

@@ -1479,8 +1479,8 @@ template <typename T, int N> struct Engine : EngineBase {
       C<T>* ky = ksp ? nullptr : dual_kernels(s, q0, nq, kc, twp, bm, "bwd_dual_kgen", "bwd_dual_kgen_y");
       prof.run("bwd_dual_xscatter", s, (double)nq * ((double)NC * cb + pts), [&] {
         if (cfg.assignment == 1)
-          k_xscatter_dual_tsc<T, Sh, WX><<<(int)(NN / WX), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf, F,
-                                                                      q0, nq, x, NC, twp);
+          k_xscatter_dual<T, Sh, WX, true><<<(int)(NN / WX), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf,
+                                                                         F, q0, nq, x, NC, twp);
         else
           k_xscatter_dual<T, Sh, WX><<<(int)(NN / WX), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf, F,
                                                                    q0, nq, x, NC, twp);
@@ -1738,7 +1738,7 @@ template <typename T, int N> struct Engine : EngineBase {
           k_strided<T, Sh, W, -1, IN_WINDOW, OUT_DENSE><<<dim3(N / W, nz, nq), NT, 0, s>>>(
               kx, ky, kx_slot, ky_slot, (int64_t)ny * N, NN, N, N, pwy(), nullptr, nullptr, 0, nullptr, twp);
           launch_check("kgen_y(multipoles adjoint)");
-          k_xscatter_dual<T, Sh, WX, true><<<(int)(NN / WX), NTX, 0, s>>>(
+          k_xscatter_dual<T, Sh, WX, false, true><<<(int)(NN / WX), NTX, 0, s>>>(
               line_set(), l_f.as<int32_t>(), cf, F, q0, nq, x, NC, twp, yl, nh, P);
           launch_check("xscatter(multipoles adjoint)");
           k_strided<T, Sh, W, -1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, nq), NT, 0, s>>>(

@@ -49,6 +49,70 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The points of several ranges of a catalogue as one index range that all
+// threads of a block walk together.  The x-direction scatters and gathers give
+// a line TPL threads, few on small grids, while a clustered catalogue puts most
+// of a block's points on one or two lines; taking every point of the block's
+// lines by any of its threads keeps the block as short as its total.
+// build(range): range(r, s, e) gives the bounds of range r < NR; returns the
+// number of points.  find(i): the range of combined index i; its point is
+// i + first[find(i)].  NT: threads of the block.
+template <int NR, int NT> struct BlockRanges {
+  int off[NR];    // combined index of the range's first point
+  int first[NR];  // its first point minus that
+  int part[NT / 64];
+  template <typename Fn> __device__ __forceinline__ int build(Fn&& range) {
+    constexpr int PER = (NR + NT - 1) / NT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int s[PER], c[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      s[k] = c[k] = 0;
+      const int r = tid * PER + k;
+      if (r < NR) {
+        int e = 0;
+        range(r, s[k], e);
+        c[k] = e - s[k];
+      }
+      sum += c[k];
+    }
+    int inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int u = __shfl_up(inc, d, 64);
+      if (lane >= d) inc += u;
+    }
+    if (lane == 63) part[wave] = inc;
+    block_sync();
+    int base = inc - sum, total = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+      const int v = part[w];
+      if (w < wave) base += v;
+      total += v;
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int r = tid * PER + k;
+      if (r < NR) {
+        off[r] = base;
+        first[r] = s[k] - base;
+      }
+      base += c[k];
+    }
+    block_sync();
+    return total;
+  }
+  __device__ __forceinline__ int find(int i) const {
+    int r = 0;
+    constexpr int TOP = NR <= 1 ? 0 : 1 << (31 - __builtin_clz(NR - 1));
+#pragma unroll
+    for (int step = TOP; step > 0; step >>= 1)
+      if (((NR & (NR - 1)) == 0 || r + step < NR) && off[r + step] <= i) r += step;
+    return r;
+  }
+};
+
 template <typename T, typename Sh>
 __device__ __forceinline__ void load_twiddles(C<T>* tw_s, const C<T>* __restrict__ tw_g) {
   for (int i = threadIdx.x; i < Sh::tw_entries(); i += blockDim.x) tw_s[i] = tw_g[i];

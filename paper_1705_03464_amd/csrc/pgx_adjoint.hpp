@@ -419,11 +419,13 @@ k_zinit(const C<T>* __restrict__ ky_in, int pwz, const C<T>* __restrict__ fg,
 }
 
 // ----------------------------------------------------------------------------
-// Inverse x pass fused with the CIC gather.  One task per non-empty line of a
+// Inverse x pass fused with the gather.  One task per non-empty line of a
 // field pair (same task words as the forward scatter).  The line is inverse
-// transformed, kept in LDS, and every point whose CIC footprint reaches the
-// line takes its share (real part for field a, imaginary for b):
+// transformed, kept in LDS, and every point whose footprint reaches the line
+// takes its share (real part for field a, imaginary for b): for CIC
 //   scale * wy * wz * ((1 - fx) line[x0] + fx line[x0 + 1]).
+// The points of all lines of a block form one index range walked by all its
+// threads (PointRanges).
 // With qs > 0 (CIC, every footprint line of every point among the tasks)
 // the share of the line at offset (dy, dz) in {0, 1}^2 from the point's base
 // line is stored to acc[(dy + 2 dz) qs + p]: each entry is written exactly
@@ -432,88 +434,65 @@ k_zinit(const C<T>* __restrict__ ky_in, int pwz, const C<T>* __restrict__ fg,
 // ----------------------------------------------------------------------------
 template <typename T, typename Sh, int W, bool TSC = false>
 static __global__ void __launch_bounds__(W * Sh::TPL)
-k_xgather(const int32_t* __restrict__ tasks, int n_tasks, PointSet<T> ps,
+k_xgather(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> ps,
           const int32_t* __restrict__ slot_fa, const int32_t* __restrict__ slot_fb,
           const C<T>* __restrict__ in, T scale, float* __restrict__ acc, int64_t qs,
           const C<T>* __restrict__ tw_g, const float* __restrict__ fscale = nullptr) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int NT = W * TPL, NB = line_sources<TSC>(), NR = W * 2 * NB;
   constexpr int64_t NN = (int64_t)N * N;
   __shared__ C<T> tw_s[Sh::tw_entries()];
-  __shared__ C<T> lines[W][LL];
+  __shared__ C<T> lines[W * LL];
+  __shared__ PointRanges<NR, NT> br;
+  __shared__ T scs[W * 2];  // scale of each line's two fields
   load_twiddles<T, Sh>(tw_s, tw_g);
-  const int t = threadIdx.x % TPL, l = threadIdx.x / TPL;
-  const int task = blockIdx.x * W + l;
+  const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
+  const int task = block_task<N, W>(l, rev);
   const bool active = task < n_tasks;
-  C<T>* line = lines[l];
-  int slot = 0, y = 0, z = 0;
-  if (active) {
-    const int32_t word = tasks[task];
-    slot = (int)(word / NN);
-    const int li = (int)(word - (int64_t)slot * NN);
-    y = li % N;
-    z = li / N;
-  }
+  C<T>* line = lines + l * LL;
+  const int32_t word = active ? tasks[task] : 0;
+  const int slot = (int)(word / NN);
+  const int li = (int)(word - (int64_t)slot * NN);
   C<T> v[E];
-  const C<T>* src = in + (int64_t)slot * NN * N + ((int64_t)z * N + y) * N;
+  const C<T>* src = in + (int64_t)slot * NN * N + (int64_t)li * N;
 #pragma unroll
   for (int m = 0; m < E; ++m) v[m] = active ? src[t + TPL * m] : C<T>{0, 0};
-  block_sync();
+  if (t < 2) {
+    // a field whose kernel coefficients were divided by fscale[f] gives
+    // values scaled by 1 / fscale[f]: undo it here
+    const int f = t == 0 ? slot_fa[slot] : slot_fb[slot];
+    scs[l * 2 + t] = scale * (fscale && f >= 0 ? (T)fscale[f] : (T)1);
+  }
+  const int total = br.build([&](int r, int& s, int& e) {
+    task_source<T, N, W, TSC>(tasks, n_tasks, rev, 0, r, slot_fa, slot_fb, ps.line_start, s, e);
+  });
   line_fft<Sh, 1>(v, t, line, tw_s, wave_sync);
-  block_sync();
+  wave_sync();  // the line's wavefront has read its last-stage inputs
 #pragma unroll
   for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = v[m];
   block_sync();
-  if (active) {
-    const int ym = (y - 1) & (N - 1), zm = (z - 1) & (N - 1);
-    const int fa = slot_fa[slot], fb = slot_fb[slot];
-#pragma unroll
-    for (int part = 0; part < 2; ++part) {
-      const int f = part == 0 ? fa : fb;
-      if (f < 0) continue;
-      const int64_t fbase = (int64_t)f * NN;
-      // a field whose kernel coefficients were divided by fscale[f] gives
-      // values scaled by 1 / fscale[f]: undo it here
-      const T sc = scale * (fscale ? (T)fscale[f] : (T)1);
-      // the base lines whose points read this line (as in the scatter)
-      constexpr int NB = TSC ? 16 : 4;
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        int by, bz;
-        if constexpr (TSC) {
-          by = (y + (q & 3) - 2) & (N - 1);
-          bz = (z + (q >> 2) - 2) & (N - 1);
-        } else {
-          by = (q & 1) ? ym : y;
-          bz = (q & 2) ? zm : z;
-        }
-        const int64_t key = fbase + (int64_t)bz * N + by;
-        const int s = ps.line_start[key], e = ps.line_start[key + 1];
-        for (int p = s + t; p < e; p += TPL) {
-          const T fy = ps.fy[p], fz = ps.fz[p], fx = ps.fx[p];
-          const int x0 = ps.x0[p];
-          auto val = [&](int xx) {
-            const C<T> a = line[lpad(xx & (N - 1))];
-            return part == 0 ? a.x : a.y;
-          };
-          if constexpr (TSC) {
-            const T wyz = tsc_line_weight<T>(by, fy, y, N) * tsc_line_weight<T>(bz, fz, z, N);
-            if (wyz == (T)0) continue;
-            T wx[3];
-            int lx;
-            tsc_axis<T>(x0, fx, lx, wx);
-            const T g = wx[0] * val(lx) + wx[1] * val(lx + 1) + wx[2] * val(lx + 2);
-            atomicAdd(&acc[p], (float)(sc * wyz * g));
-          } else {
-            const T wy = (q & 1) ? fy : (T)1 - fy;
-            const T wz = (q & 2) ? fz : (T)1 - fz;
-            const float g = (float)(sc * wy * wz * (((T)1 - fx) * val(x0) + fx * val(x0 + 1)));
-            if (qs > 0)
-              acc[q * qs + p] = g;
-            else
-              atomicAdd(&acc[p], g);
-          }
-        }
-      }
+  typename PointRanges<NR, NT>::Walk walk;
+#pragma unroll 2
+  for (int i = tid; i < total; i += NT) {
+    const int p = walk.point(br, i);
+    const int q = walk.r % NB, lp = walk.r / NB;  // lp = 2 l + part
+    const T fy = ps.fy[p], fz = ps.fz[p], fx = ps.fx[p];
+    const int x0 = ps.x0[p];
+    const T* ln = reinterpret_cast<const T*>(lines + (lp >> 1) * LL) + (lp & 1);
+    auto val = [&](int xx) { return ln[2 * lpad(xx & (N - 1))]; };
+    const T w = scs[lp] * source_weight<T, TSC>(q, fy, fz, N);
+    if constexpr (TSC) {
+      if (w == (T)0) continue;
+      T wx[3];
+      int lx;
+      tsc_axis<T>(x0, fx, lx, wx);
+      atomicAdd(&acc[p], (float)(w * (wx[0] * val(lx) + wx[1] * val(lx + 1) + wx[2] * val(lx + 2))));
+    } else {
+      const float g = (float)(w * (((T)1 - fx) * val(x0) + fx * val(x0 + 1)));
+      if (qs > 0)
+        acc[q * qs + p] = g;
+      else
+        atomicAdd(&acc[p], g);
     }
   }
 }

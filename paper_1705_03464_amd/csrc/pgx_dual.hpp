@@ -489,7 +489,7 @@ __device__ __forceinline__ T pick3(const T* w, int j) {
 }
 
 // x pass of the Pi fields with the scatter fused in.  Block = W neighbouring
-// lines (y, z), each for every slot of the batch in turn (bins 2(q0+slot),
+// lines (y, z), each for its slots of the batch in turn (bins 2(q0+slot),
 // 2(q0+slot)+1): the lines are built in LDS from the points whose footprint
 // reaches them, each weighted by its pair weight and its field's coefficient
 // pair, transformed along x and written.  Every one of the N*N lines is
@@ -505,12 +505,13 @@ __device__ __forceinline__ T pick3(const T* w, int j) {
 //
 // What bounds it: the points of the few crowded lines of a clustered
 // catalogue, a chain of loads and LDS atomics, not the dense output.  So all
-// points of the block's lines form one index range that all its threads walk
-// together (BlockRanges), whatever line they belong to: with TPL threads per
+// points of a wavefront's lines form one index range that its lanes walk
+// together (PointRanges), whatever line they belong to, or the whole block
+// where one wavefront has most of them (scatter_together): with TPL threads per
 // line a 256^3 grid left a crowded line to 32 threads.  Contributions of
 // points on the same x node are summed across the wavefront first (the points
 // of a source line run in x order), and only the last lane of each run adds
-// to LDS.  The first KEEP points of every thread stay in registers across
+// to LDS.  The first KEEP points of every lane stay in registers across
 // the slots, their coefficients loaded one slot ahead; further points are
 // read again per slot, the next trip's in flight during the current one.
 template <typename T, typename Sh, int W, bool TSC = false, bool HARM = false>
@@ -520,20 +521,26 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
                 const C<T>* __restrict__ tw_g, const float* __restrict__ yl = nullptr, int nh = 1,
                 int64_t P = 0) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr int NT = W * TPL, NB = TSC ? 9 : 4, NX = TSC ? 3 : 2, NR = W * NB, KEEP = 2;
+  constexpr int NT = W * TPL, NB = TSC ? 9 : 4, NX = TSC ? 3 : 2, KEEP = 2;
+  // 512^3 and larger: enough blocks to hide a crowded line (3.36 ms per launch
+  // without the second mode, 3.52 with it; 256^3: 0.66 and 0.59)
+  constexpr bool TOGETHER = N < 512;
+  constexpr int LW = 64 / TPL, NR = LW * NB;  // lines and sources of a wavefront
   static_assert(N % W == 0, "the lines of a block share their z row");
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W * LL];
-  __shared__ BlockRanges<NR, NT> br;
+  __shared__ PointRanges<NR, 64> wave_ranges[NT / 64];
   load_twiddles<T, Sh>(tw_s, tw_g);
-  const int tid = threadIdx.x, t = tid % TPL, l = tid / TPL;
+  const int tid = threadIdx.x, lane = tid & 63, t = tid % TPL, l = tid / TPL;
+  const int l0 = (tid >> 6) * LW;  // the wavefront's first line
+  PointRanges<NR, 64>& br = wave_ranges[tid >> 6];
   const int li = blockIdx.x * W + l;  // < N*N by the grid
   const int y_base = (int)(blockIdx.x * W) % N, z = (int)(blockIdx.x * W) / N;
   C<T>* line = lines + l * LL;
 #pragma unroll
   for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
   const int total = br.build([&](int r, int& s, int& e) {
-    const int q = r % NB, y = y_base + r / NB;
+    const int q = r % NB, y = y_base + l0 + r / NB;
     const int by = (TSC ? y + q % 3 - 1 : y - (q & 1)) & (N - 1);
     const int bz = (TSC ? z + q / 3 - 1 : z - (q >> 1)) & (N - 1);
     const int k = bz * N + by;
@@ -547,10 +554,10 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
     int f, p;
     bool on;
   };
-  auto fetch = [&](int i) {
+  auto fetch = [&](const PointRanges<NR, 64>& pr, int count, typename PointRanges<NR, 64>::Walk& walk, int i) {
     Point a;
-    a.on = i < total;
-    a.key = NR * N + tid;  // idle lanes: past every real key, each its own
+    a.on = i < count;
+    a.key = NR * N + lane;  // idle lanes: past every real key, each its own
     a.f = 0;
     a.p = 0;
 #pragma unroll
@@ -559,7 +566,7 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
       a.at[j] = 0;
     }
     if (a.on) {
-      const int r = br.find(i), q = r % NB, p = i + br.first[r], base = (r / NB) * LL;
+      const int p = walk.point(pr, i), r = walk.r, q = r % NB, base = (l0 + r / NB) * LL;
       const T fx = ps.fx[p], fy = ps.fy[p], fz = ps.fz[p];
       const int x0 = ps.x0[p];
       const T wt = ps.wt ? ps.wt[p] : (T)1;
@@ -609,42 +616,70 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
       }
     }
   };
+  // this block's slots of the batch
+  const int slot_lo = (int)(nq * blockIdx.y / gridDim.y), slot_hi = (int)(nq * (blockIdx.y + 1) / gridDim.y);
+  typename PointRanges<NR, 64>::Walk walk;
   Point kept[KEEP];
   WaveRuns runs[KEEP];
   float2 cn[KEEP];
 #pragma unroll
   for (int k = 0; k < KEEP; ++k) {
-    kept[k] = fetch(tid + k * NT);
+    kept[k] = fetch(br, total, walk, lane + k * 64);
     runs[k].init(kept[k].key);
-    cn[k] = kept[k].on ? coef[(int64_t)q0 * F + kept[k].f] : float2{0.f, 0.f};
+    cn[k] = kept[k].on ? coef[(int64_t)(q0 + slot_lo) * F + kept[k].f] : float2{0.f, 0.f};
   }
-  for (int slot = 0; slot < nq; ++slot) {
-    const float2* cq = coef + (int64_t)(q0 + slot) * F;
-    block_sync();  // the lines are zero
-#pragma unroll
-    for (int k = 0; k < KEEP; ++k) {
-      if (k * NT >= total) break;
-      const float2 c = cn[k];
-      if (kept[k].on && slot + 1 < nq) cn[k] = cq[F + kept[k].f];
-      add(kept[k], runs[k], c, slot);
+  // points first, first + step, .. of the ranges `pr` into this wavefront's lines
+  auto scatter = [&](const PointRanges<NR, 64>& pr, typename PointRanges<NR, 64>::Walk wk, int first, int step,
+                     const float2* cq, int slot) {
+    const int count = pr.count;
+    Point a = fetch(pr, count, wk, first + lane);
+    for (int base = first; base < count; base += step) {
+      const float2 c = a.on ? cq[a.f] : float2{0.f, 0.f};
+      const Point nx = fetch(pr, count, wk, base + step + lane);
+      WaveRuns r;
+      r.init(a.key);
+      add(a, r, c, slot);
+      a = nx;
     }
-    if (KEEP * NT < total) {
-      Point a = fetch(KEEP * NT + tid);
-      for (int base = KEEP * NT; base < total; base += NT) {
-        const float2 c = a.on ? cq[a.f] : float2{0.f, 0.f};
-        const Point nx = fetch(base + NT + tid);
-        WaveRuns r;
-        r.init(a.key);
-        add(a, r, c, slot);
-        a = nx;
+  };
+  block_sync();  // twiddles, every wavefront's ranges
+  const bool together = TOGETHER && scatter_together<NR, NT / 64>(wave_ranges);
+  for (int slot = slot_lo; slot < slot_hi; ++slot) {
+    const float2* cq = coef + (int64_t)(q0 + slot) * F;
+    C<T> v[E];
+    wave_sync();  // the lines are zero; a line belongs to one wavefront
+    if (!together) {
+#pragma unroll
+      for (int k = 0; k < KEEP; ++k) {
+        if (k * 64 >= total) break;
+        const float2 c = cn[k];
+        if (kept[k].on && slot + 1 < slot_hi) cn[k] = cq[F + kept[k].f];
+        add(kept[k], runs[k], c, slot);
+      }
+      if (KEEP * 64 < total) scatter(br, walk, KEEP * 64, 64, cq, slot);
+      wave_sync();
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[m] = line[lpad(t + TPL * m)];
+      wave_sync();
+    } else {
+      for (int g = 0; g < NT / 64; ++g) {
+        scatter(wave_ranges[g], typename PointRanges<NR, 64>::Walk(), tid & ~63, NT, cq, slot);
+        block_sync();
+        if (l0 == g * LW) {
+#pragma unroll
+          for (int m = 0; m < E; ++m) v[m] = C<T>{0, 0};
+          for (int u = 0; u < NT / 64; ++u) {
+            const C<T>* copy = lines + (u * LW + l - l0) * LL;
+#pragma unroll
+            for (int m = 0; m < E; ++m) v[m] = cadd(v[m], copy[lpad(t + TPL * m)]);
+          }
+        }
+        block_sync();
+#pragma unroll
+        for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
+        wave_sync();
       }
     }
-    block_sync();
-    // each line belongs to one wavefront from here to the next slot's scatter
-    C<T> v[E];
-#pragma unroll
-    for (int m = 0; m < E; ++m) v[m] = line[lpad(t + TPL * m)];
-    wave_sync();
     line_fft<Sh, -1>(v, t, line, tw_s, wave_sync);
     C<T>* o = out + (int64_t)slot * out_slot + (int64_t)li * N;
 #pragma unroll

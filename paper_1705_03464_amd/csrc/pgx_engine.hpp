@@ -271,7 +271,6 @@ template <typename T, int N> struct Engine : EngineBase {
   // the (field, line) starts that only the per-field transforms read (built
   // with their task lists)
   DBuf p_key, p_ls, p_fs, p_i, p_j, p_x0, p_fx, p_fy, p_fz, p_wt;
-  DBuf tasks_s, t_key, t_key2;  // the scatter's task order (most crowded line first) and its sort keys
   DBuf p_wd, wg_part;  // FP64 pair weights of the current forward; partial weight sums
   DBuf ws_part, red_part, mp_part;  // partial sums of the chunked segmented reductions
   // line-major copy of the pair catalogue (all fields together): line starts,
@@ -341,8 +340,7 @@ template <typename T, int N> struct Engine : EngineBase {
     b += pd * (16.0 + 4.0 * tb + 8.0 + 12.0 + 4.0 * tb + 16.0);
     // per-(field, line) starts, counting table, line flags, task positions
     const double fl = F * NN + 1.0, pl = nfp * NN + 1.0;
-    // (and the task order's keys, sorted copies and sort temporaries)
-    b += fl * 4.0 + (std::max({ncell, fl, (double)NN}) + 1.0) * 8.0 + pl * (1.0 + 4.0 + 4.0 + 24.0) + nfp * N +
+    b += fl * 4.0 + (std::max({ncell, fl, (double)NN}) + 1.0) * 8.0 + pl * (1.0 + 4.0 + 4.0) + nfp * N +
          2.0 * (NN + 1.0) * 4.0;
     const double tiny = 16.0 * F * R * 8.0 + 4.0 * (F + R) * 8.0 + ((size_t)8 << 20);
     if (c.precision == PGX_FP64_PLAIN) {
@@ -655,7 +653,7 @@ template <typename T, int N> struct Engine : EngineBase {
     if (tasks_ready) fpr.insert(fpr.end(), batch_task_off.begin(), batch_task_off.end());
     fpr.insert(fpr.end(), field_counts_h.begin(), field_counts_h.end());
     for (const DBuf* d : {&g_key, &g_ls, &g_x0, &g_fx, &g_fy, &g_fz, &g_idx, &g_wt, &g_tasks, &p_key,
-                          &p_ls, &p_fs, &p_i, &p_j, &p_x0, &p_fx, &p_fy, &p_fz, &p_wt, &lflag, &pflag, &tasks, &tasks_s, &l_ls, &l_x0, &l_fx,
+                          &p_ls, &p_fs, &p_i, &p_j, &p_x0, &p_fx, &p_fy, &p_fz, &p_wt, &lflag, &pflag, &tasks, &l_ls, &l_x0, &l_fx,
                           &l_fy, &l_fz, &l_f, &l_p, &l_wt})
       fpr.push_back((int64_t)(intptr_t)d->p);
     if (fpr != build_print) {
@@ -992,27 +990,6 @@ template <typename T, int N> struct Engine : EngineBase {
     int32_t* tk = tasks.get<int32_t>(ntk);
     k_emit_tasks<<<grid_for(nfl), 256, 0, s>>>(lf, pos, nfl, N, B, tk);
     launch_check("emit_tasks");
-    // the scatter's copy: within each batch most crowded line first (stable,
-    // so equal counts keep line order), so that a clustered catalogue's few
-    // crowded lines start early instead of trailing the launch and the lines
-    // sharing a block have similar point counts (6.6 against 7.8 ms per
-    // launch on 3.6e8 HOD pairs).  The adjoint's gather keeps line order,
-    // where the four lines that read a point's records run close together
-    // and find them in cache (6.0 against 6.3 ms).
-    int32_t* tks = tasks_s.get<int32_t>(ntk);
-    PGX_HIP(hipMemcpyAsync(tks, tk, (size_t)ntk * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    if (hpos[n_batches] > 0) {
-      int32_t* key = t_key.get<int32_t>(ntk);
-      int32_t* key2 = t_key2.get<int32_t>(ntk);
-      k_task_cost<<<grid_for(nfl), 256, 0, s>>>(lf, pos, nfl, N, cfg.F, cfg.assignment == 1 ? 4 : 2,
-                                                p_ls.as<int32_t>(), key);
-      launch_check("task_cost");
-      for (int k = 0; k < n_batches; ++k) {
-        const int64_t t0 = hpos[k], nt = hpos[k + 1] - t0;
-        if (nt < 2) continue;
-        sort_pairs_i32(key + t0, key2 + t0, tk + t0, tks + t0, nt, kTaskKeyBits, s, s_tmp);
-      }
-    }
     tasks_ready = true;
   }
 
@@ -1022,6 +999,18 @@ template <typename T, int N> struct Engine : EngineBase {
     int64_t n = 0;
     for (int f = 2 * k * B; f < std::min(2 * (k + 1) * B, cfg.F); ++f) n += field_counts_h[f];
     return n;
+  }
+
+  // whether the later field pairs of batch k hold most of its pairs (as with
+  // ascending separation bins): its x-pass tasks then run last first, so that
+  // the launch ends on short lines
+  int last_crowded(int k) const {
+    if (field_counts_h.empty()) return 0;
+    const int f0 = 2 * k * B, f1 = std::min(2 * (k + 1) * B, cfg.F), fm = (f0 + f1) / 2;
+    int64_t a = 0, b = 0;
+    for (int f = f0; f < fm; ++f) a += field_counts_h[f];
+    for (int f = fm; f < f1; ++f) b += field_counts_h[f];
+    return b > a ? 1 : 0;
   }
 
   static int bits_for(int64_t nkeys) {
@@ -1094,22 +1083,34 @@ template <typename T, int N> struct Engine : EngineBase {
 
   // x-pass scatter and its adjoint gather with the plan's mass assignment
   // (CIC, or TSC on the same point records)
-  void xscatter(int grid, const int32_t* tk, int nt, const PointSet<T>& ps, const int32_t* fa,
+  void xscatter(int grid, const int32_t* tk, int nt, int rev, const PointSet<T>& ps, const int32_t* fa,
                 const int32_t* fb, C<T>* out, const C<T>* twp, const float* fsc, hipStream_t s) {
     if (cfg.assignment == 1)
-      k_xscatter<T, Sh, WX, true><<<grid, NTX, 0, s>>>(tk, nt, ps, fa, fb, out, twp, fsc);
+      k_xscatter<T, Sh, WX, true><<<grid, NTX, 0, s>>>(tk, nt, rev, ps, fa, fb, out, twp, fsc);
     else
-      k_xscatter<T, Sh, WX><<<grid, NTX, 0, s>>>(tk, nt, ps, fa, fb, out, twp, fsc);
+      k_xscatter<T, Sh, WX><<<grid, NTX, 0, s>>>(tk, nt, rev, ps, fa, fb, out, twp, fsc);
   }
   // (CIC: the four per-line shares of each point to acc[q qs + p], written
   // once each; TSC: added to acc[p] with atomics)
-  void xgather(int grid, const int32_t* tk, int nt, const PointSet<T>& ps, const int32_t* fa,
+  void xgather(int grid, const int32_t* tk, int nt, int rev, const PointSet<T>& ps, const int32_t* fa,
                const int32_t* fb, const C<T>* in, T scale, float* acc, int64_t qs, const C<T>* twp,
                const float* fsc, hipStream_t s) {
     if (cfg.assignment == 1)
-      k_xgather<T, Sh, WX, true><<<grid, NTX, 0, s>>>(tk, nt, ps, fa, fb, in, scale, acc, 0, twp, fsc);
+      k_xgather<T, Sh, WX, true><<<grid, NTX, 0, s>>>(tk, nt, rev, ps, fa, fb, in, scale, acc, 0, twp, fsc);
     else
-      k_xgather<T, Sh, WX><<<grid, NTX, 0, s>>>(tk, nt, ps, fa, fb, in, scale, acc, qs, twp, fsc);
+      k_xgather<T, Sh, WX><<<grid, NTX, 0, s>>>(tk, nt, rev, ps, fa, fb, in, scale, acc, qs, twp, fsc);
+  }
+
+  // Grid of the Pi scatter: NN / WX blocks of lines, the slots split over
+  // blockIdx.y until the launch has about kDualScatterBlocks blocks.  A block
+  // with a crowded line outlasts the others by its points times its slots;
+  // splitting costs reading every point once per part.  256^3 (8192 blocks of
+  // lines, 10 slots): 0.64 ms whole, 0.54 in 2 parts, 0.56 in 5, 0.61 in 10
+  // (TSC 1.59, 1.23, 1.15, 1.22); 512^3 (65536 blocks): 3.22 whole, 3.39 in 2.
+  static constexpr int kDualScatterBlocks = 24576;
+  static dim3 dual_scatter_grid(int nq) {
+    const int nb = (int)(NN / WX);
+    return dim3(nb, std::max(1, std::min(nq, kDualScatterBlocks / nb)), 1);
   }
 
   PointSet<T> gal_set() const {
@@ -1365,7 +1366,7 @@ template <typename T, int N> struct Engine : EngineBase {
         } else {
           if (nt > 0) {
             prof.run("bwd_xscatter", s, pts + (double)nt * N * cb, [&] {
-              xscatter((int)((nt + WX - 1) / WX), tasks_s.as<int32_t>() + t0, (int)nt, pair_set(), fa, fb,
+              xscatter((int)((nt + WX - 1) / WX), tasks.as<int32_t>() + t0, (int)nt, last_crowded(k), pair_set(), fa, fb,
                        x, twp, FSC.as<float>(), s);
               launch_check("xscatter(bwd)");
             });
@@ -1390,7 +1391,7 @@ template <typename T, int N> struct Engine : EngineBase {
           // point records (x0, fractions) read, the per-line shares written
           const double gpts = (double)batch_points(k) * (4.0 + 3.0 * sizeof(T) + 4.0 * gcomp);
           prof.run("bwd_xgather", s, gpts + (double)nt * N * cb, [&] {
-            xgather((int)((nt + WX - 1) / WX), tasks.as<int32_t>() + t0, (int)nt, pair_set(), fa, fb, x,
+            xgather((int)((nt + WX - 1) / WX), tasks.as<int32_t>() + t0, (int)nt, last_crowded(k), pair_set(), fa, fb, x,
                     (T)1, gb, gstride, twp, FSC.as<float>(), s);
             launch_check("xgather");
           });
@@ -1429,7 +1430,7 @@ template <typename T, int N> struct Engine : EngineBase {
       launch_check("gal_yinv");
     });
     prof.run("bwd_gal_xgather", s, (double)NC * cb + (double)n_gal * (4 + 4 * sizeof(T)), [&] {
-      xgather((int)(NN / WX), g_tasks.as<int32_t>(), (int)NN, gal_set(), gslot_fa.as<int32_t>(),
+      xgather((int)(NN / WX), g_tasks.as<int32_t>(), (int)NN, 0, gal_set(), gslot_fa.as<int32_t>(),
               gslot_fb.as<int32_t>(), A, (T)2, gbg, ggstride, twp, nullptr, s);
       launch_check("gal_xgather");
     });
@@ -1479,10 +1480,10 @@ template <typename T, int N> struct Engine : EngineBase {
       C<T>* ky = ksp ? nullptr : dual_kernels(s, q0, nq, kc, twp, bm, "bwd_dual_kgen", "bwd_dual_kgen_y");
       prof.run("bwd_dual_xscatter", s, (double)nq * ((double)NC * cb + pts), [&] {
         if (cfg.assignment == 1)
-          k_xscatter_dual<T, Sh, WX, true><<<(int)(NN / WX), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf,
+          k_xscatter_dual<T, Sh, WX, true><<<dual_scatter_grid(nq), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf,
                                                                          F, q0, nq, x, NC, twp);
         else
-          k_xscatter_dual<T, Sh, WX><<<(int)(NN / WX), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf, F,
+          k_xscatter_dual<T, Sh, WX><<<dual_scatter_grid(nq), NTX, 0, s>>>(line_set(), l_f.as<int32_t>(), cf, F,
                                                                    q0, nq, x, NC, twp);
         launch_check("xscatter(dual adjoint)");
       });
@@ -1738,7 +1739,7 @@ template <typename T, int N> struct Engine : EngineBase {
           k_strided<T, Sh, W, -1, IN_WINDOW, OUT_DENSE><<<dim3(N / W, nz, nq), NT, 0, s>>>(
               kx, ky, kx_slot, ky_slot, (int64_t)ny * N, NN, N, N, pwy(), nullptr, nullptr, 0, nullptr, twp);
           launch_check("kgen_y(multipoles adjoint)");
-          k_xscatter_dual<T, Sh, WX, false, true><<<(int)(NN / WX), NTX, 0, s>>>(
+          k_xscatter_dual<T, Sh, WX, false, true><<<dual_scatter_grid(nq), NTX, 0, s>>>(
               line_set(), l_f.as<int32_t>(), cf, F, q0, nq, x, NC, twp, yl, nh, P);
           launch_check("xscatter(multipoles adjoint)");
           k_strided<T, Sh, W, -1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, nq), NT, 0, s>>>(
@@ -1879,7 +1880,7 @@ template <typename T, int N> struct Engine : EngineBase {
     // ---- galaxy field: spectrum (DC removed) and auto-correlation
     const double cb = (double)sizeof(C<T>);
     prof.run("gal_xscatter", s, (double)n_gal * (4 + 4 * sizeof(T)) + (double)NC * cb, [&] {
-      xscatter((int)(NN / WX), g_tasks.as<int32_t>(), (int)NN, gal_set(), gslot_fa.as<int32_t>(),
+      xscatter((int)(NN / WX), g_tasks.as<int32_t>(), (int)NN, 0, gal_set(), gslot_fa.as<int32_t>(),
                gslot_fb.as<int32_t>(), x, twp, nullptr, s);
       launch_check("xscatter(gal)");
     });
@@ -1921,7 +1922,7 @@ template <typename T, int N> struct Engine : EngineBase {
       const double pts = (double)batch_points(k) * (4 + 4 * sizeof(T));
       if (nt > 0) {
         prof.run("xscatter", s, pts + (double)nt * N * cb, [&] {
-          xscatter((int)((nt + WX - 1) / WX), tasks_s.as<int32_t>() + t0, (int)nt, pair_set(), fa, fb, x,
+          xscatter((int)((nt + WX - 1) / WX), tasks.as<int32_t>() + t0, (int)nt, last_crowded(k), pair_set(), fa, fb, x,
                    twp, FSC.as<float>(), s);
           launch_check("xscatter");
         });

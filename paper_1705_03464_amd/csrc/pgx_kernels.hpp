@@ -49,21 +49,28 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The points of several ranges of a catalogue as one index range that all
-// threads of a block walk together.  The x-direction scatters and gathers give
-// a line TPL threads, few on small grids, while a clustered catalogue puts most
-// of a block's points on one or two lines; taking every point of the block's
-// lines by any of its threads keeps the block as short as its total.
+// The points of several ranges of a catalogue as one index range that NT
+// threads walk together: one wavefront (NT = 64) or the whole block.  The
+// x-direction passes give a line TPL threads, few on small grids, while a
+// clustered catalogue puts most of a block's points on one or two lines.  The
+// gathers share the points of a block's lines among all its threads; the
+// scatters share those of a wavefront's lines within it, so that a line's LDS
+// additions come from one wavefront and keep their order from run to run.
 // build(range): range(r, s, e) gives the bounds of range r < NR; returns the
-// number of points.  find(i): the range of combined index i; its point is
-// i + first[find(i)].  NT: threads of the block.
-template <int NR, int NT> struct BlockRanges {
+// number of points.  A Walk follows ascending combined indices, searching only
+// when it leaves a range.
+template <int NR, int NT> struct PointRanges {
   int off[NR];    // combined index of the range's first point
   int first[NR];  // its first point minus that
   int part[NT / 64];
+  int count;      // all points
+  __device__ __forceinline__ static void sync() {
+    if constexpr (NT == 64) wave_sync();
+    else block_sync();
+  }
   template <typename Fn> __device__ __forceinline__ int build(Fn&& range) {
     constexpr int PER = (NR + NT - 1) / NT;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x % NT, lane = tid & 63;
     int s[PER], c[PER], sum = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -82,14 +89,17 @@ template <int NR, int NT> struct BlockRanges {
       const int u = __shfl_up(inc, d, 64);
       if (lane >= d) inc += u;
     }
-    if (lane == 63) part[wave] = inc;
-    block_sync();
-    int base = inc - sum, total = 0;
+    int base = inc - sum, total = __shfl(inc, 63, 64);
+    if constexpr (NT > 64) {
+      if (lane == 63) part[tid >> 6] = inc;
+      block_sync();
+      total = 0;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-      const int v = part[w];
-      if (w < wave) base += v;
-      total += v;
+      for (int w = 0; w < NT / 64; ++w) {
+        const int v = part[w];
+        if (w < tid >> 6) base += v;
+        total += v;
+      }
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -100,7 +110,8 @@ template <int NR, int NT> struct BlockRanges {
       }
       base += c[k];
     }
-    block_sync();
+    if (tid == 0) count = total;
+    sync();
     return total;
   }
   __device__ __forceinline__ int find(int i) const {
@@ -111,7 +122,36 @@ template <int NR, int NT> struct BlockRanges {
       if (((NR & (NR - 1)) == 0 || r + step < NR) && off[r + step] <= i) r += step;
     return r;
   }
+  struct Walk {
+    int r = 0, next = 0, shift = 0;
+    // point of combined index i (ascending from call to call); its range is r
+    __device__ __forceinline__ int point(const PointRanges& b, int i) {
+      if (i >= next) {
+        r = b.find(i);
+        next = r + 1 < NR ? b.off[r + 1] : 0x7FFFFFFF;
+        shift = b.first[r];
+      }
+      return i + shift;
+    }
+  };
 };
+
+// Whether the NW wavefronts of a scatter block take the wavefronts' points one
+// after another together, each into its own copy of the lines, instead of each
+// its own: trips of 64 NW points plus the copies' sum and two barriers per
+// wavefront (about three trips), against the trips of the most crowded one.
+// Depends on the points only, so every run adds in the same order.
+template <int NR, int NW>
+__device__ __forceinline__ bool scatter_together(const PointRanges<NR, 64>* wave_ranges) {
+  int most = 0, trips = 0;
+#pragma unroll
+  for (int g = 0; g < NW; ++g) {
+    const int n = wave_ranges[g].count;
+    most = n > most ? n : most;
+    trips += n / (64 * NW) + 4;
+  }
+  return trips < most / 64;
+}
 
 template <typename T, typename Sh>
 __device__ __forceinline__ void load_twiddles(C<T>* tw_s, const C<T>* __restrict__ tw_g) {
@@ -246,131 +286,168 @@ __device__ __forceinline__ T tsc_line_weight(int a0, T f, int a, int N) {
 }
 
 // ----------------------------------------------------------------------------
-// (A) x pass with the CIC scatter fused in.  One task per non-empty line of a
-// field pair.  The line is built in LDS from the points of the four base lines
-// whose CIC footprint reaches it (LDS atomics), transformed along x and
-// written once.  task word = slot * N*N + line (line = z*N + y).  When a line
-// is one or more whole wavefronts, each wavefront first sums the
-// contributions of adjacent points on the same x node (clustered catalogues
-// put many points on one node, and same-address LDS atomics serialise), and
-// only the last point of each run adds to the line.
+// Sources of the x-pass lines l0, l0 + 1, .. of a block: range
+// r = ((l - l0) 2 + part) NB + q holds the points of base line q of field
+// `part` (0 real, 1 imaginary) of line l's task, task word = slot * N*N + line (line = z*N + y).  The base lines (CIC corner
+// rows) whose points reach line (y, z): (y, z) and its lower neighbours for
+// CIC (q: the y / z weight is the upper one when bit 0 / bit 1 is set);
+// y - 2 .. y + 1 by z - 2 .. z + 1 for TSC, whose footprint of three rows
+// starts one row below or at the corner row.
+// ----------------------------------------------------------------------------
+template <bool TSC> constexpr int line_sources() { return TSC ? 16 : 4; }
+
+// Task of line l of a block of W lines.  Tasks come in line order, and a block's
+// threads share its points, so what matters is which lines meet in a block:
+//  - grids below 256^3 (few blocks, everything in the caches): lines spread
+//    evenly over the task list, so that the neighbouring crowded lines of a
+//    cluster fall into different blocks (64^3, 9000 galaxies: 21 us per launch,
+//    28 in line order, 61 with the most crowded lines first);
+//  - larger grids: neighbouring lines, which read the same points, and runs of
+//    kTaskChunk blocks of them on one XCD, so the points come from its L2
+//    (1024^3, 16 fields: 18.7 ms per step, 21.3 with the most crowded first in
+//    the hardware's block order).
+// rev: blocks in descending order (Engine::last_crowded; 3.7e8 HOD pairs at
+// 512^3: 7.9 ms per step, 8.5 ascending).
+constexpr int kTaskChunk = 32;
+template <int N, int W> __device__ __forceinline__ int block_task(int l, int rev) {
+  const int b = rev ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+  if constexpr (N < 256) {
+    return b + l * (int)gridDim.x;
+  } else {
+    // block b runs on XCD b mod 8: whole rounds of 8 chunks are permuted
+    const int whole = (int)gridDim.x / (8 * kTaskChunk) * (8 * kTaskChunk), k = b >> 3;
+    const int lb = b < whole ? ((k / kTaskChunk) * 8 + (b & 7)) * kTaskChunk + k % kTaskChunk : b;
+    return lb * W + l;
+  }
+}
+
+template <typename T, int N, int W, bool TSC>
+__device__ __forceinline__ void task_source(const int32_t* __restrict__ tasks, int n_tasks, int rev, int l0, int r,
+                                            const int32_t* __restrict__ slot_fa,
+                                            const int32_t* __restrict__ slot_fb,
+                                            const int32_t* __restrict__ line_start, int& s, int& e) {
+  constexpr int NB = line_sources<TSC>();
+  constexpr int64_t NN = (int64_t)N * N;
+  const int task = block_task<N, W>(l0 + r / (2 * NB), rev), q = r % NB;
+  s = e = 0;
+  if (task >= n_tasks) return;
+  const int32_t word = tasks[task];
+  const int slot = (int)(word / NN), li = (int)(word - (int64_t)slot * NN);
+  const int f = (r / NB) & 1 ? slot_fb[slot] : slot_fa[slot];
+  if (f < 0) return;
+  const int y = li % N, z = li / N;
+  const int by = (TSC ? y + (q & 3) - 2 : y - (q & 1)) & (N - 1);
+  const int bz = (TSC ? z + (q >> 2) - 2 : z - (q >> 1)) & (N - 1);
+  const int64_t key = (int64_t)f * NN + (int64_t)bz * N + by;
+  s = line_start[key];
+  e = line_start[key + 1];
+}
+// y and z weight of a point of source q on its line
+template <typename T, bool TSC> __device__ __forceinline__ T source_weight(int q, T fy, T fz, int N) {
+  if constexpr (TSC)
+    return tsc_line_weight<T>((q & 3) - 2, fy, 0, N) * tsc_line_weight<T>((q >> 2) - 2, fz, 0, N);
+  else
+    return ((q & 1) ? fy : (T)1 - fy) * ((q & 2) ? fz : (T)1 - fz);
+}
+
+// ----------------------------------------------------------------------------
+// (A) x pass with the mass assignment fused in.  One task per non-empty line
+// of a field pair.  The lines are built in LDS from the points whose footprint
+// reaches them (LDS atomics), transformed along x and written once.  The
+// points of all lines of a wavefront form one index range walked by all its
+// lanes (PointRanges): on the tiny candidate set (64^3, 8 threads per line)
+// the launch lasted as long as the most crowded line's own threads.  Each
+// wavefront first sums the contributions of adjacent points on the same x
+// node (clustered catalogues put many points on one node, and same-address
+// LDS atomics serialise), and only the last point of each run adds to the
+// line.  The next trip's points are in flight during the current one.
 // ----------------------------------------------------------------------------
 template <typename T, typename Sh, int W, bool TSC = false>
 static __global__ void __launch_bounds__(W * Sh::TPL)
-k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, PointSet<T> ps,
+k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> ps,
            const int32_t* __restrict__ slot_fa, const int32_t* __restrict__ slot_fb,
            C<T>* __restrict__ out, const C<T>* __restrict__ tw_g,
            const float* __restrict__ fscale = nullptr) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int NT = W * TPL, NB = line_sources<TSC>(), NX = TSC ? 3 : 2;
+  constexpr int LW = 64 / TPL, NR = LW * 2 * NB;  // lines and sources of a wavefront
   constexpr int64_t NN = (int64_t)N * N;
-  constexpr bool kRuns = TPL % 64 == 0;
   __shared__ C<T> tw_s[Sh::tw_entries()];
-  __shared__ C<T> lines[W][LL];
+  __shared__ C<T> lines[W * LL];
+  __shared__ PointRanges<NR, 64> wave_ranges[NT / 64];
+  __shared__ T scs[W * 2];  // transform scale of each line's two fields
   load_twiddles<T, Sh>(tw_s, tw_g);
-  const int t = threadIdx.x % TPL, l = threadIdx.x / TPL;
-  const int task = blockIdx.x * W + l;
+  const int tid = threadIdx.x, lane = tid & 63, t = tid % TPL, l = tid / TPL;
+  const int l0 = (tid >> 6) * LW;  // the wavefront's first line
+  PointRanges<NR, 64>& br = wave_ranges[tid >> 6];
+  const int task = block_task<N, W>(l, rev);
   const bool active = task < n_tasks;
-  C<T>* line = lines[l];
+  C<T>* line = lines + l * LL;
 #pragma unroll
   for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
-  int slot = 0, y = 0, z = 0;
-  if (active) {
-    const int32_t word = tasks[task];
-    slot = (int)(word / NN);
-    const int li = (int)(word - (int64_t)slot * NN);
-    y = li % N;
-    z = li / N;
+  const int32_t word = active ? tasks[task] : 0;
+  const int slot = (int)(word / NN);
+  const int li = (int)(word - (int64_t)slot * NN);
+  if (t < 2) {
+    const int f = t == 0 ? slot_fa[slot] : slot_fb[slot];
+    scs[l * 2 + t] = fscale && f >= 0 ? (T)fscale[f] : (T)1;
   }
-  block_sync();
-  if (active) {
-    const int ym = (y - 1) & (N - 1), zm = (z - 1) & (N - 1);
-    const int fa = slot_fa[slot], fb = slot_fb[slot];
-#pragma unroll
-    for (int part = 0; part < 2; ++part) {
-      const int f = part == 0 ? fa : fb;
-      if (f < 0) continue;
-      const int64_t fbase = (int64_t)f * NN;
-      const T sc = fscale ? (T)fscale[f] : (T)1;
-      // base lines (CIC corner rows) whose points reach this line: (y, z) and
-      // their lower neighbours for CIC; y - 2 .. y + 1 by z - 2 .. z + 1 for
-      // TSC, whose footprint of three rows starts one row below or at the
-      // corner row
-      constexpr int NB = TSC ? 16 : 4;
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        int by, bz;
-        if constexpr (TSC) {
-          by = (y + (q & 3) - 2) & (N - 1);
-          bz = (z + (q >> 2) - 2) & (N - 1);
-        } else {
-          by = (q & 1) ? ym : y;
-          bz = (q & 2) ? zm : z;
-        }
-        const int64_t key = fbase + (int64_t)bz * N + by;
-        const int s = ps.line_start[key], e = ps.line_start[key + 1];
-        // every lane of a wavefront takes the same trips (one line per wavefront)
-        for (int b0 = s; b0 < e; b0 += TPL) {
-          const int p = b0 + t;
-          const bool ok = p < e;
-          T lo = (T)0, mid = (T)0, hi = (T)0;
-          int x0 = -1 - (int)(threadIdx.x & 63u);  // idle lanes: keys no node has
-          if (ok) {
-            const T fy = ps.fy[p], fz = ps.fz[p], fx = ps.fx[p];
-            x0 = ps.x0[p];
-            if constexpr (TSC) {
-              const T w = ps.wt[p] * sc * tsc_line_weight<T>(by, fy, y, N) *
-                          tsc_line_weight<T>(bz, fz, z, N);
-              // nodes c - 1, c, c + 1 of the nearest node c; the run key is c
-              T wx[3];
-              int lx;
-              tsc_axis<T>(x0, fx, lx, wx);
-              x0 = (lx + 1) & (N - 1);
-              lo = w * wx[0];
-              mid = w * wx[1];
-              hi = w * wx[2];
-            } else {
-              const T wy = (q & 1) ? fy : (T)1 - fy;
-              const T wz = (q & 2) ? fz : (T)1 - fz;
-              const T w = ps.wt[p] * sc * wy * wz;
-              lo = w * ((T)1 - fx);
-              hi = w * fx;
-            }
-          }
-          bool issue = ok;
-          if constexpr (kRuns) {
-            SegRuns r;
-            r.init(x0);
-            lo = r.add(lo);
-            if constexpr (TSC) mid = r.add(mid);
-            hi = r.add(hi);
-            issue = ok && r.tail;
-          }
-          if (issue) {
-            auto at = [&](int xx) -> T* {
-              C<T>* c = &line[lpad(xx & (N - 1))];
-              return part == 0 ? &c->x : &c->y;
-            };
-            if constexpr (TSC) {
-              atomicAdd(at(x0 - 1), lo);
-              atomicAdd(at(x0), mid);
-              atomicAdd(at(x0 + 1), hi);
-            } else {
-              atomicAdd(at(x0), lo);
-              atomicAdd(at(x0 + 1), hi);
-            }
-          }
-        }
-      }
+  const int total = br.build([&](int r, int& s, int& e) {
+    task_source<T, N, W, TSC>(tasks, n_tasks, rev, l0, r, slot_fa, slot_fb, ps.line_start, s, e);
+  });
+  struct Point {
+    T fx, fy, fz, wt, sc;
+    int x0, r;
+  };
+  typename PointRanges<NR, 64>::Walk walk;
+  auto fetch = [&](int i) {
+    Point a{(T)0, (T)0, (T)0, (T)0, (T)0, 0, -1};
+    if (i < total) {
+      const int p = walk.point(br, i);
+      a.r = walk.r;
+      a.sc = scs[2 * l0 + walk.r / NB];
+      a.fx = ps.fx[p];
+      a.fy = ps.fy[p];
+      a.fz = ps.fz[p];
+      a.wt = ps.wt[p];
+      a.x0 = ps.x0[p];
     }
-  }
+    return a;
+  };
+  // twiddles; no barrier follows, so no wavefront waits for a crowded one
   block_sync();
+  Point a = fetch(lane);
+  for (int base = 0; base < total; base += 64) {
+    const Point nx = fetch(base + 64 + lane);
+    const bool ok = a.r >= 0;
+    const int r = ok ? a.r : 0, q = r % NB, lp = 2 * l0 + r / NB;  // lp = 2 line + part
+    const T w = a.wt * a.sc * source_weight<T, TSC>(q, a.fy, a.fz, N);
+    T wx[NX];
+    int lo = a.x0;
+    if constexpr (TSC) {
+      tsc_axis<T>(a.x0, a.fx, lo, wx);
+    } else {
+      wx[0] = (T)1 - a.fx;
+      wx[1] = a.fx;
+    }
+    SegRuns runs;
+    runs.init(ok ? r * N + ((lo + NX - 2) & (N - 1)) : -1 - lane);
+    T* dst = reinterpret_cast<T*>(lines + (lp >> 1) * LL) + (lp & 1);
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      const T v = runs.add(w * wx[j]);
+      if (ok && runs.tail) atomicAdd(dst + 2 * lpad((lo + j) & (N - 1)), v);
+    }
+    a = nx;
+  }
+  wave_sync();  // a line belongs to one wavefront
   C<T> v[E];
 #pragma unroll
   for (int m = 0; m < E; ++m) v[m] = line[lpad(t + TPL * m)];
-  block_sync();
+  wave_sync();
   line_fft<Sh, -1>(v, t, line, tw_s, wave_sync);
   if (active) {
-    C<T>* o = out + (int64_t)slot * NN * N + ((int64_t)z * N + y) * N;
+    C<T>* o = out + (int64_t)slot * NN * N + (int64_t)li * N;
 #pragma unroll
     for (int m = 0; m < E; ++m) o[t + TPL * m] = v[m];
   }

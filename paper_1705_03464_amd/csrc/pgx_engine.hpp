@@ -633,9 +633,10 @@ template <typename T, int N> struct Engine : EngineBase {
       double* wp = p_wd.get<double>(std::max<int64_t>(P, 1));
       const int K = reduce_chunks(F);
       double* part = ws_part.get<double>((int64_t)F * K);
-      k_pair_wts<T><<<dim3(F, K), 256, 0, s>>>(p_fs.as<int32_t>(), p_i.as<int32_t>(), p_j.as<int32_t>(), w,
-                                               nullptr, wp, part);
-      k_sum_chunks<<<grid_for(F), 256, 0, s>>>(part, F, K, wsum);
+      k_weights<T><<<std::max(F * K, 1), 256, 0, s>>>(w, n, 0, nullptr, p_fs.as<int32_t>(), F, K,
+                                                      p_i.as<int32_t>(), p_j.as<int32_t>(), nullptr, wp, part,
+                                                      nullptr, nullptr);
+      k_weight_sums<<<weight_sums_grid(F), 256, 0, s>>>(part, F, K, wsum, nullptr, nullptr, nullptr);
       launch_check("field_wsum");
     }
     PGX_HIP(hipStreamSynchronize(s));
@@ -1059,26 +1060,17 @@ template <typename T, int N> struct Engine : EngineBase {
   // ------------------------------------------------------------------------
   void weights(const float* w, hipStream_t s) {
     const int F = cfg.F;
-    if (n_gal > 0) {
-      k_gather_weights<T><<<grid_for(n_gal), 256, 0, s>>>(g_idx.as<int32_t>(), w, n_gal, g_wt.as<T>());
-      launch_check("gal_weights");
-    }
     double* wp = p_wd.get<double>(std::max<int64_t>(n_pairs, 1));
-    {
-      // pair weights (FP64, and in T for the scatters) with their per-field sums
-      const int K = reduce_chunks(F);
-      double* part = ws_part.get<double>((int64_t)F * K);
-      k_pair_wts<T><<<dim3(F, K), 256, 0, s>>>(p_fs.as<int32_t>(), p_i.as<int32_t>(), p_j.as<int32_t>(), w,
-                                               n_pairs > 0 ? p_wt.as<T>() : nullptr, wp, part);
-      k_sum_chunks<<<grid_for(F), 256, 0, s>>>(part, F, K, wsum_d.get<double>(F));
-      launch_check("pair_weights");
-    }
-    k_field_scale<<<grid_for(F), 256, 0, s>>>(wsum_d.as<double>(), F, FSC.get<float>(std::max(F, 1)));
-    launch_check("field_scale");
+    // chunks per field of the pair-weight sums
+    const int K = reduce_chunks(F);
+    double* part = ws_part.get<double>((int64_t)F * K);
     double* wpart = wg_part.get<double>(kWtBlocks);
-    k_weight_partial<<<kWtBlocks, 256, 0, s>>>(w, n_gal, wpart);
-    k_weight_total<<<1, 256, 0, s>>>(wpart, wg_d.get<double>(1));
-    launch_check("weight_total");
+    k_weights<T><<<kWtBlocks + F * K + (n_gal > 0 ? grid_for(n_gal) : 0), 256, 0, s>>>(
+        w, n_gal, kWtBlocks, wpart, p_fs.as<int32_t>(), F, K, p_i.as<int32_t>(), p_j.as<int32_t>(),
+        n_pairs > 0 ? p_wt.as<T>() : nullptr, wp, part, g_idx.as<int32_t>(), g_wt.as<T>());
+    k_weight_sums<<<weight_sums_grid(F), 256, 0, s>>>(part, F, K, wsum_d.get<double>(F),
+                                                      FSC.get<float>(std::max(F, 1)), wpart, wg_d.get<double>(1));
+    launch_check("weights");
   }
 
   // x-pass scatter and its adjoint gather with the plan's mass assignment
@@ -1304,13 +1296,15 @@ template <typename T, int N> struct Engine : EngineBase {
     aa.apg = apg.get<double>((int64_t)F * R);
     aa.agg = agg.get<double>(R);
     aa.gws = gws.get<double>(F);
-    aa.gwg = gwg.get<double>(1);
-    k_finalize_adjoint<<<1, 256, 0, s>>>(aa);
+    aa.gwg = gwg.get<double>(F + R);
+    aa.clear = gd;
+    aa.n_clear = std::max<int64_t>(n_gal, 1);
+    k_finalize_adjoint<<<finalize_adjoint_grid(F, R, aa.n_clear), 64, 0, s>>>(aa);
     launch_check("finalize_adjoint");
-    if (gcomp == 1)
+    if (gcomp == 1 && !fwd_dual) {  // the TSC gather adds; the dual form writes every pair
       k_fill_value<float><<<grid_for(gstride), 256, 0, s>>>(gb, gstride, 0.f);
-    k_fill_value<double><<<grid_for(std::max<int64_t>(n_gal, 1)), 256, 0, s>>>(gd, std::max<int64_t>(n_gal, 1), 0.0);
-    launch_check("fill");
+      launch_check("fill");
+    }
     // galaxy kernel field -> A = K^_g G (on the kernel-spectrum path of the
     // dual form the z pass of the pairs computes K^_g G from the stored
     // spectra instead)
@@ -1398,16 +1392,16 @@ template <typename T, int N> struct Engine : EngineBase {
         }
       }
     }
-    galaxy_adjoint_tail(s, A, gb, gcomp, gd, aa.gws, aa.gwg, grad_w, twp);
+    galaxy_adjoint_tail(s, A, gb, gcomp, gd, aa.gws, aa.gwg, F + R, grad_w, twp);
   }
 
   // Galaxy side and weight chain of the adjoint, after A holds the spectral
   // accumulation: dL/drho_g = 2 Re IDFT(A) with A(0) removed, gathered at the
   // galaxies; then the per-galaxy gradient from the pair terms (gb, pair
-  // weights w_i w_j, dL/dWsum_f) and the galaxy terms (dL/dW_g).
+  // weights w_i w_j, dL/dWsum_f) and the galaxy terms (dL/dW_g: n_gwg parts).
   // gb: the pair-side values, gcomp components of stride max(n_pairs, 1).
   void galaxy_adjoint_tail(hipStream_t s, C<T>* A, const float* gb, int gcomp, double* gd,
-                           const double* gws_d, const double* gwg_d, float* grad_w, const C<T>* twp) {
+                           const double* gws_d, const double* gwg_d, int n_gwg, float* grad_w, const C<T>* twp) {
     const double cb = (double)sizeof(C<T>);
     // galaxy-side values: one share per footprint line (CIC), or one sum (TSC)
     const int ggcomp = cfg.assignment == 0 ? 4 : 1;
@@ -1442,7 +1436,7 @@ template <typename T, int N> struct Engine : EngineBase {
       launch_check("pair_grad");
     }
     if (n_gal > 0) {
-      k_gal_grad<<<grid_for(n_gal), 256, 0, s>>>(g_idx.as<int32_t>(), gbg, ggcomp, ggstride, n_gal, gwg_d, gd);
+      k_gal_grad<<<grid_for(n_gal), 256, 0, s>>>(g_idx.as<int32_t>(), gbg, ggcomp, ggstride, n_gal, gwg_d, n_gwg, gd);
       k_grad_out<<<grid_for(n_gal), 256, 0, s>>>(gd, n_gal, grad_w);
       launch_check("grad_out");
     }
@@ -1668,7 +1662,7 @@ template <typename T, int N> struct Engine : EngineBase {
         double* part = mp_part.get<double>((int64_t)F * R * nl * K);
         k_dual_reduce_mp<<<dim3(F, R * nl, K), 256, 0, s>>>(p_fs.as<int32_t>(), 1, p_wd.as<double>(), gv, yp,
                                                             P, R, nh, nl, mp_scale.as<float>(), part);
-        k_sum_chunks<<<grid_for((int64_t)F * R * nl), 256, 0, s>>>(part, (int64_t)F * R * nl, K, Sm);
+        k_sum_chunks<<<sum_chunks_grid((int64_t)F * R * nl, K), 256, 0, s>>>(part, (int64_t)F * R * nl, K, Sm);
         launch_check("reduce(multipoles)");
       }
       k_finalize_mp<<<grid_for((int64_t)F * R * nl), 256, 0, s>>>(Sm, nbd.as<double>(), wsum_d.as<double>(),
@@ -1749,7 +1743,7 @@ template <typename T, int N> struct Engine : EngineBase {
           launch_check("zacc(multipoles adjoint)");
         }
       }
-      galaxy_adjoint_tail(s, A, gb, 1, gd, gws_d, gwg_d, grad_w, twp);
+      galaxy_adjoint_tail(s, A, gb, 1, gd, gws_d, gwg_d, 1, grad_w, twp);
     }
   }
 
@@ -1855,7 +1849,7 @@ template <typename T, int N> struct Engine : EngineBase {
     double* part = red_part.get<double>((int64_t)F * R * K);
     k_dual_reduce<<<dim3(F, R, K), 256, 0, s>>>(p_fs.as<int32_t>(), 1, p_wd.as<double>(), gv, n_pairs,
                                                 R, bscale.as<float>(), part);
-    k_sum_chunks<<<grid_for((int64_t)F * R), 256, 0, s>>>(part, (int64_t)F * R, K, Sd);
+    k_sum_chunks<<<sum_chunks_grid((int64_t)F * R, K), 256, 0, s>>>(part, (int64_t)F * R, K, Sd);
     launch_check("reduce(dual)");
     if (kc) kc_valid = true;
   }

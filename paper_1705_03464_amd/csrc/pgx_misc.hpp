@@ -1,6 +1,7 @@
 // Smaller kernels: weights, deterministic FP64 reductions, the finalisation
 // formulas, and the pieces of the plain one-field-at-a-time path.
 #pragma once
+#include "pgx_host.hpp"
 #include "pgx_kernels.hpp"
 
 namespace pgx {
@@ -62,15 +63,6 @@ static __global__ void k_validate_w(const float* __restrict__ w, int64_t n, int*
 // ----------------------------------------------------------------------------
 // weights
 // ----------------------------------------------------------------------------
-// pair weight w_i * w_j (exact in FP64 for FP32 weights), rounded to T
-template <typename T>
-static __global__ void k_gather_weights(const int32_t* __restrict__ idx, const float* __restrict__ w,
-                                 int64_t n, T* __restrict__ out) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  out[p] = w ? (T)w[idx[p]] : (T)1;
-}
-
 // Deterministic block sum of a double per thread (fixed tree over 256 lanes).
 __device__ __forceinline__ double block_sum256(double v, double* sh) {
   sh[threadIdx.x] = v;
@@ -99,37 +91,109 @@ __device__ __forceinline__ void chunk_of(int64_t s, int64_t e, int k, int K, int
   cs = s + (e - s) * k / K;
   ce = s + (e - s) * (k + 1) / K;
 }
-// out[i] = sum_{k < K} part[i K + k], in order
+// Sum over the lanes of a wavefront, the same on every lane (fixed tree).
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+// sum_{k < K} part[k] by one wavefront (fixed order: strided lanes, then the tree)
+__device__ __forceinline__ double wave_sum_chunks(const double* __restrict__ part, int K) {
+  double a = 0.0;
+  for (int k = (int)(threadIdx.x & 63u); k < K; k += 64) a += part[k];
+  return wave_sum(a);
+}
+// out[i] = sum_{k < K} part[i K + k]: few chunks by one thread in order, many
+// (few segments) by one wavefront (20 segments of 205 chunks: 45 us by one
+// thread each, a chain of loads; 5 us by a wavefront).  sum_chunks_grid gives
+// the blocks of 256 threads.
+constexpr int kChunksPerThread = 8;
+__host__ inline int sum_chunks_grid(int64_t n, int K) { return grid_for(K <= kChunksPerThread ? n : n * 64); }
 static __global__ void k_sum_chunks(const double* __restrict__ part, int64_t n, int K,
                                     double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (K <= kChunksPerThread) {
+    if (t >= n) return;
+    double a = 0.0;
+    for (int k = 0; k < K; ++k) a += part[t * K + k];
+    out[t] = a;
+    return;
+  }
+  const int64_t i = t >> 6;
   if (i >= n) return;
-  double a = 0.0;
-  for (int k = 0; k < K; ++k) a += part[i * K + k];
-  out[i] = a;
+  const double a = wave_sum_chunks(part + i * K, K);
+  if ((threadIdx.x & 63u) == 0) out[i] = a;
 }
 
-// Pair weights w_i w_j (FP64 products, unit without weights; also rounded
-// to T into wt when it is given) and their partial sums over each field's
-// range: block (f, k) of a grid (F, K) takes chunk k of field f.  fs: the
-// field starts of the field-major pair catalogue.
+// Everything a forward derives from the galaxy weights w (unit without), in
+// one launch over three kinds of blocks of 256 threads:
+//  - kWtBlocks blocks (n_total of them, 0 to leave this out): the FP64 partial
+//    sums of w over fixed contiguous chunks;
+//  - F K blocks: the pair weights w_i w_j of chunk k of field f (FP64 products,
+//    also rounded to T into wt when it is given) and their partial sum; fs:
+//    the field starts of the field-major pair catalogue;
+//  - the rest: the galaxies' weights in catalogue order of the point set.
+// k_weight_sums adds the partial sums.  Small catalogues pay per launch (about
+// 5 us each), so these run as two launches instead of six.
+constexpr int kWtBlocks = 256;
 template <typename T>
-static __global__ void k_pair_wts(const int32_t* __restrict__ fs, const int32_t* __restrict__ pi,
-                                  const int32_t* __restrict__ pj, const float* __restrict__ w,
-                                  T* __restrict__ wt, double* __restrict__ wd, double* __restrict__ part) {
+static __global__ void k_weights(const float* __restrict__ w, int64_t n, int n_total, double* __restrict__ wpart,
+                                 const int32_t* __restrict__ fs, int F, int K, const int32_t* __restrict__ pi,
+                                 const int32_t* __restrict__ pj, T* __restrict__ wt, double* __restrict__ wd,
+                                 double* __restrict__ part, const int32_t* __restrict__ idx,
+                                 T* __restrict__ gal_wt) {
   __shared__ double sh[256];
-  const int f = blockIdx.x, k = blockIdx.y, K = gridDim.y;
-  int64_t cs, ce;
-  chunk_of(fs[f], fs[f + 1], k, K, cs, ce);
-  double acc = 0.0;
-  for (int64_t p = cs + threadIdx.x; p < ce; p += 256) {
-    const double d = w ? (double)w[pi[p]] * (double)w[pj[p]] : 1.0;
-    wd[p] = d;
-    if (wt) wt[p] = (T)d;
-    acc += d;
+  int b = (int)blockIdx.x;
+  if (b < n_total) {
+    const int64_t chunk = (n + kWtBlocks - 1) / kWtBlocks;
+    const int64_t lo = (int64_t)b * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    double acc = 0.0;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) acc += w ? (double)w[i] : 1.0;
+    const double r = block_sum256(acc, sh);
+    if (threadIdx.x == 0) wpart[b] = r;
+    return;
   }
-  const double r = block_sum256(acc, sh);
-  if (threadIdx.x == 0) part[(int64_t)f * K + k] = r;
+  b -= n_total;
+  if (b < F * K) {
+    const int f = b % F, k = b / F;
+    int64_t cs, ce;
+    chunk_of(fs[f], fs[f + 1], k, K, cs, ce);
+    double acc = 0.0;
+    for (int64_t p = cs + threadIdx.x; p < ce; p += 256) {
+      const double d = w ? (double)w[pi[p]] * (double)w[pj[p]] : 1.0;
+      wd[p] = d;
+      if (wt) wt[p] = (T)d;
+      acc += d;
+    }
+    const double r = block_sum256(acc, sh);
+    if (threadIdx.x == 0) part[(int64_t)f * K + k] = r;
+    return;
+  }
+  const int64_t p = (int64_t)(b - F * K) * 256 + threadIdx.x;
+  if (p < n) gal_wt[p] = w ? (T)w[idx[p]] : (T)1;
+}
+// The sums of k_weights' partials: one wavefront per field (wsum, and its
+// transform scale 1 / Wsum_f rounded to FP32, 1 for empty fields, so that the
+// two fields sharing a complex grid have unit mass each and neither one's
+// rounding swamps the other's signal), and the total weight in the last block
+// (when wg is given).  Grid: weight_sums_grid(F).
+__host__ inline int weight_sums_grid(int F) { return (F + 3) / 4 + 1; }
+static __global__ void k_weight_sums(const double* __restrict__ part, int F, int K, double* __restrict__ wsum,
+                                     float* __restrict__ fsc, const double* __restrict__ wpart,
+                                     double* __restrict__ wg) {
+  __shared__ double sh[256];
+  if (blockIdx.x == gridDim.x - 1) {
+    if (!wg) return;
+    const double r = block_sum256(wpart[threadIdx.x], sh);  // kWtBlocks = 256 partial sums
+    if (threadIdx.x == 0) wg[0] = r;
+    return;
+  }
+  const int f = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (f >= F) return;
+  const double a = wave_sum_chunks(part + (int64_t)f * K, K);
+  if ((threadIdx.x & 63u) != 0) return;
+  wsum[f] = a;
+  if (fsc) fsc[f] = (float)(a > 1e-30 ? 1.0 / a : 1.0);
 }
 
 // Largest disagreement between two sets of bin sums of the same estimator,
@@ -161,34 +225,6 @@ static __global__ void k_xi_disagreement(const double* __restrict__ Sa, const do
   if (threadIdx.x == 0) out[0] = sh[0];
 }
 
-// Per-field scale of the pair fields in the transforms: 1 / Wsum_f rounded to
-// FP32 (1 for empty fields), so that the two fields sharing a complex grid
-// have unit mass each and neither one's rounding swamps the other's signal.
-static __global__ void k_field_scale(const double* __restrict__ wsum, int F, float* __restrict__ fsc) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f < F) fsc[f] = (float)(wsum[f] > 1e-30 ? 1.0 / wsum[f] : 1.0);
-}
-
-// Sum of galaxy weights in FP64, deterministic: kWtBlocks blocks each sum a
-// fixed contiguous chunk (256 threads, fixed partition), then one block sums
-// the partials in order.
-constexpr int kWtBlocks = 256;
-static __global__ void k_weight_partial(const float* __restrict__ w, int64_t n, double* __restrict__ part) {
-  __shared__ double sh[256];
-  const int64_t chunk = (n + kWtBlocks - 1) / kWtBlocks;
-  const int64_t a = (int64_t)blockIdx.x * chunk, b = a + chunk < n ? a + chunk : n;
-  double acc = 0.0;
-  for (int64_t i = a + threadIdx.x; i < b; i += 256) acc += w ? (double)w[i] : 1.0;
-  const double r = block_sum256(acc, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = r;
-}
-static __global__ void k_weight_total(const double* __restrict__ part, double* __restrict__ out) {
-  __shared__ double sh[256];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < kWtBlocks; i += 256) acc += part[i];
-  const double r = block_sum256(acc, sh);
-  if (threadIdx.x == 0) out[0] = r;
-}
 // ----------------------------------------------------------------------------
 // bin partial reduction: part[slot][nblk][2][R] -> S[f][R] for the two fields
 // of each slot (fixed order over blocks, deterministic)

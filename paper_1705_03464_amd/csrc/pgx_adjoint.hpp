@@ -230,7 +230,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
         int64_t ky_slot, int pwz, const C<T>* __restrict__ fg, C<T>* __restrict__ acc_out,
         const C<T>* __restrict__ tw_g, const C<T>* __restrict__ spec = nullptr) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   constexpr bool PIPE = E <= 8;  // register room for a second set of columns
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
@@ -264,15 +264,15 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
   block_sync();
   const int64_t col = (int64_t)ky * N + xt * W + c;
   // buffer path for fields up to 2 GiB per slot (see k_zcross)
-  constexpr bool BUF = NN * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
+  constexpr bool BUF = ZS * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr uint32_t CB = sizeof(C<T>);
-  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * NN * CB) : 0u;  // TPL planes
+  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * ZS * CB) : 0u;  // TPL planes
   const int64_t tile = (int64_t)ky * N + xt * W;
-  const uint32_t vo = (uint32_t)((c + (int64_t)t * NN) * CB);
+  const uint32_t vo = (uint32_t)((c + (int64_t)t * ZS) * CB);
   auto load_cols = [&](int slot, bool take, C<T>* dst) {
     if constexpr (STORED) {
       // the stored spectrum Z of this slot's field pair (dense)
-      const C<T>* zs = spec + (int64_t)slot_fp[slot] * (NN * N);
+      const C<T>* zs = spec + (int64_t)slot_fp[slot] * (ZS * N);
       if constexpr (BUF) {
         const Buf<T> bz(zs + tile);
         const uint32_t kill = take ? 0u : kBufOff;
@@ -280,7 +280,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
         for (int m = 0; m < E; ++m) dst[m] = bz.load((vo + (uint32_t)m * ZST) | kill, 0u);
       } else {
 #pragma unroll
-        for (int m = 0; m < E; ++m) dst[m] = zs[col + (int64_t)(t + TPL * m) * NN];
+        for (int m = 0; m < E; ++m) dst[m] = zs[col + (int64_t)(t + TPL * m) * ZS];
       }
       return;
     }
@@ -294,7 +294,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
       // absent planes read the tile's first element (valid), zeroed when taken
       const C<T>* src = x + slot * x_slot + col;
 #pragma unroll
-      for (int m = 0; m < E; ++m) dst[m] = src[(mk >> m) & 1u ? (int64_t)(t + TPL * m) * NN : 0];
+      for (int m = 0; m < E; ++m) dst[m] = src[(mk >> m) & 1u ? (int64_t)(t + TPL * m) * ZS : 0];
     }
   };
   auto take_cols = [&](int slot, const C<T>* cur, C<T>* v) {
@@ -337,7 +337,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     if constexpr (BUF) g[m] = Buf<T>(fg + tile).load(vo, (uint32_t)m * ZST);
-    else g[m] = fg[col + (int64_t)(t + TPL * m) * NN];
+    else g[m] = fg[col + (int64_t)(t + TPL * m) * ZS];
   }
   auto body = [&](int slot, C<T>* v, C<T>* k) {
     if constexpr (!STORED) {
@@ -363,7 +363,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
     } else {
       C<T>* xs = x + slot * x_slot + col;
 #pragma unroll
-      for (int m = 0; m < E; ++m) xs[(int64_t)(t + TPL * m) * NN] = v[m];
+      for (int m = 0; m < E; ++m) xs[(int64_t)(t + TPL * m) * ZS] = v[m];
     }
   };
   if constexpr (PIPE) {
@@ -394,7 +394,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
   }
 #pragma unroll
   for (int m = 0; m < E; ++m) {
-    C<T>* p = acc_out + col + (int64_t)(t + TPL * m) * NN;
+    C<T>* p = acc_out + col + (int64_t)(t + TPL * m) * ZS;
     const C<T> o = *p, a = ACC_LDS ? accs[c][t + TPL * m] : accr[ACC_LDS ? 0 : m];
     *p = C<T>{o.x + a.x, o.y + a.y};
   }
@@ -407,7 +407,7 @@ static __global__ void __launch_bounds__(W * Sh::TPL)
 k_zinit(const C<T>* __restrict__ ky_in, int pwz, const C<T>* __restrict__ fg,
         C<T>* __restrict__ acc_out, const C<T>* __restrict__ tw_g) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
   load_twiddles<T, Sh>(tw_s, tw_g);
@@ -429,7 +429,7 @@ k_zinit(const C<T>* __restrict__ ky_in, int pwz, const C<T>* __restrict__ fg,
   line_fft<Sh, -1>(k, t, lines[c], tw_s, block_sync);
 #pragma unroll
   for (int m = 0; m < E; ++m) {
-    const int64_t idx = col + (int64_t)(t + TPL * m) * NN;
+    const int64_t idx = col + (int64_t)(t + TPL * m) * ZS;
     const C<T> gv = fg[idx];
     acc_out[idx] = C<T>{k[m].x * gv.x, k[m].x * gv.y};
   }
@@ -471,7 +471,7 @@ k_xgather(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> p
   const int slot = (int)(word / NN);
   const int li = (int)(word - (int64_t)slot * NN);
   C<T> v[E];
-  const C<T>* src = in + (int64_t)slot * NN * N + (int64_t)li * N;
+  const C<T>* src = in + ((int64_t)slot * N + li / N) * plane_stride<T, N>() + (int64_t)(li % N) * N;
 #pragma unroll
   for (int m = 0; m < E; ++m) v[m] = active ? src[t + TPL * m] : C<T>{0, 0};
   if (t < 2) {
@@ -497,7 +497,7 @@ k_xgather(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> p
     const int x0 = ps.x0[p];
     const T* ln = reinterpret_cast<const T*>(lines + (lp >> 1) * LL) + (lp & 1);
     auto val = [&](int xx) { return ln[2 * lpad(xx & (N - 1))]; };
-    const T w = scs[lp] * source_weight<T, TSC>(q, fy, fz, N);
+    const T w = source_weight<T, TSC>(scs[lp], q, fy, fz, N);
     if constexpr (TSC) {
       if (w == (T)0) continue;
       T wx[3];

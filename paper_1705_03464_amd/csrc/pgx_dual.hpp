@@ -50,7 +50,7 @@ k_zconv(const C<T>* __restrict__ ky_in, int64_t ky_slot, int n_slots, int pwz,
         const C<T>* __restrict__ fg, C<T>* __restrict__ out, int64_t out_slot,
         const C<T>* __restrict__ tw_g) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   constexpr bool PIPE = E <= 8;
   __shared__ C<T> tw_s[tw_lds_entries<Sh, kZTwReg>()];
   __shared__ C<T> lines[W][LL];
@@ -60,11 +60,11 @@ k_zconv(const C<T>* __restrict__ ky_in, int64_t ky_slot, int n_slots, int pwz,
   TwAuto<Sh, T, kZTwReg> twa;
   twa.init(tw_s, tw_g, t);
   const int64_t col = (int64_t)ky * N + xt * W + c;
-  constexpr bool BUF = NN * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
+  constexpr bool BUF = ZS * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr uint32_t CB = sizeof(C<T>);
-  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * NN * CB) : 0u;
+  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * ZS * CB) : 0u;
   const int64_t tile = (int64_t)ky * N + xt * W;
-  const uint32_t vo = (uint32_t)((c + (int64_t)t * NN) * CB);
+  const uint32_t vo = (uint32_t)((c + (int64_t)t * ZS) * CB);
   // kernel columns of one slot; planes outside the window, and every plane
   // when `take` is false, are zero
   auto load_k = [&](int slot, bool take, C<T>* k) {
@@ -92,7 +92,7 @@ k_zconv(const C<T>* __restrict__ ky_in, int64_t ky_slot, int n_slots, int pwz,
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     if constexpr (BUF) g[m] = Buf<T>(fg + tile).load(vo, (uint32_t)m * ZST);
-    else g[m] = fg[col + (int64_t)(t + TPL * m) * NN];
+    else g[m] = fg[col + (int64_t)(t + TPL * m) * ZS];
   }
   auto body = [&](int slot, C<T>* v) {
     block_sync();
@@ -108,7 +108,7 @@ k_zconv(const C<T>* __restrict__ ky_in, int64_t ky_slot, int n_slots, int pwz,
     } else {
       C<T>* dst = out + slot * out_slot + col;
 #pragma unroll
-      for (int m = 0; m < E; ++m) dst[(int64_t)(t + TPL * m) * NN] = v[m];
+      for (int m = 0; m < E; ++m) dst[(int64_t)(t + TPL * m) * ZS] = v[m];
     }
   };
   if constexpr (PIPE) {
@@ -154,7 +154,6 @@ k_xinv_gather_sweep(PointSet<T> ps, const int32_t* __restrict__ perm, int64_t P,
                     const C<T>* __restrict__ U, int64_t u_slot, int zlen, int b0, int R,
                     float* __restrict__ gv, const C<T>* __restrict__ tw_g) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), NG = YT + 1;
-  constexpr int64_t NN = (int64_t)N * N;
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> rows[2][NG][LL];
   load_twiddles<T, Sh>(tw_s, tw_g);
@@ -171,7 +170,7 @@ k_xinv_gather_sweep(PointSet<T> ps, const int32_t* __restrict__ perm, int64_t P,
   float* g2 = gv + (int64_t)b2 * P;
   // row z of this group's line into registers
   auto load_row = [&](int z, C<T>* v) {
-    const C<T>* src = us + ((int64_t)(z & (N - 1)) * N + y) * N;
+    const C<T>* src = us + (int64_t)(z & (N - 1)) * plane_stride<T, N>() + (int64_t)y * N;
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = src[t + TPL * m];
   };
@@ -277,7 +276,7 @@ k_xinv_gather_sweep_tsc(PointSet<T> ps, const int32_t* __restrict__ perm, int64_
   float* g1 = gv + (int64_t)b1 * P;
   float* g2 = gv + (int64_t)b2 * P;
   auto load_row = [&](int z, C<T>* v) {
-    const C<T>* src = us + ((int64_t)(z & (N - 1)) * N + y) * N;
+    const C<T>* src = us + (int64_t)(z & (N - 1)) * plane_stride<T, N>() + (int64_t)y * N;
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = src[t + TPL * m];
   };
@@ -534,7 +533,6 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
   const int tid = threadIdx.x, lane = tid & 63, t = tid % TPL, l = tid / TPL;
   const int l0 = (tid >> 6) * LW;  // the wavefront's first line
   PointRanges<NR, 64>& br = wave_ranges[tid >> 6];
-  const int li = blockIdx.x * W + l;  // < N*N by the grid
   const int y_base = (int)(blockIdx.x * W) % N, z = (int)(blockIdx.x * W) / N;
   C<T>* line = lines + l * LL;
 #pragma unroll
@@ -681,7 +679,7 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
       }
     }
     line_fft<Sh, -1>(v, t, line, tw_s, wave_sync);
-    C<T>* o = out + (int64_t)slot * out_slot + (int64_t)li * N;
+    C<T>* o = out + (int64_t)slot * out_slot + z * plane_stride<T, N>() + (int64_t)(y_base + l) * N;
 #pragma unroll
     for (int m = 0; m < E; ++m) o[t + TPL * m] = v[m];
     wave_sync();
@@ -701,7 +699,7 @@ k_zdual_acc(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
             const C<T>* __restrict__ ky_in, int64_t ky_slot, int pwz, C<T>* __restrict__ acc_out,
             const C<T>* __restrict__ tw_g) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   constexpr bool PIPE = E <= 8;
   __shared__ C<T> tw_s[tw_lds_entries<Sh, kZTwReg>()];
   __shared__ C<T> lines[W][LL];
@@ -711,11 +709,11 @@ k_zdual_acc(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
   TwAuto<Sh, T, kZTwReg> twa;
   twa.init(tw_s, tw_g, t);
   const int64_t col = (int64_t)ky * N + xt * W + c;
-  constexpr bool BUF = NN * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
+  constexpr bool BUF = ZS * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr uint32_t CB = sizeof(C<T>);
-  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * NN * CB) : 0u;
+  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * ZS * CB) : 0u;
   const int64_t tile = (int64_t)ky * N + xt * W;
-  const uint32_t vo = (uint32_t)((c + (int64_t)t * NN) * CB);
+  const uint32_t vo = (uint32_t)((c + (int64_t)t * ZS) * CB);
   // Pi columns of one slot (zero when `take` is false)
   auto load_pi = [&](int slot, bool take, C<T>* v) {
     if constexpr (BUF) {
@@ -726,7 +724,7 @@ k_zdual_acc(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
     } else {
 #pragma unroll
       for (int m = 0; m < E; ++m) {
-        const C<T> b = x[slot * x_slot + col + (int64_t)(t + TPL * m) * NN];
+        const C<T> b = x[slot * x_slot + col + (int64_t)(t + TPL * m) * ZS];
         v[m].x = take ? b.x : (T)0;
         v[m].y = take ? b.y : (T)0;
       }
@@ -797,7 +795,7 @@ k_zdual_acc(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
   }
 #pragma unroll
   for (int m = 0; m < E; ++m) {
-    C<T>* p = acc_out + col + (int64_t)(t + TPL * m) * NN;
+    C<T>* p = acc_out + col + (int64_t)(t + TPL * m) * ZS;
     const C<T> o = *p;
     *p = C<T>{o.x + acc[m].x, o.y + acc[m].y};
   }
@@ -883,7 +881,7 @@ static __global__ void __launch_bounds__(W * Sh::TPL, Sh::E <= 8 ? 8 : 1)
 k_zconv_ks(const C<T>* __restrict__ ks, int64_t ks_slot, int n_slots, const C<T>* __restrict__ fg,
            C<T>* __restrict__ out, int64_t out_slot, const C<T>* __restrict__ tw_g) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), H = N / 2;
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   __shared__ C<T> tw_s[tw_lds_entries<Sh, false>()];
   __shared__ C<T> lines[W][LL];
   int xt, ky;
@@ -893,12 +891,12 @@ k_zconv_ks(const C<T>* __restrict__ ks, int64_t ks_slot, int n_slots, const C<T>
   twa.init(tw_s, tw_g, t);
   const int kyr = ky <= H ? ky : N - ky, x = xt * W + c;
   const int64_t col = (int64_t)ky * N + x;
-  constexpr bool BUF = NN * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
+  constexpr bool BUF = ZS * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr bool BUFK = (int64_t)(H + 1) * (H + 1) * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr uint32_t CB = sizeof(C<T>);
-  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * NN * CB) : 0u;
+  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * ZS * CB) : 0u;
   const int64_t tile = (int64_t)ky * N + xt * W;
-  const uint32_t vo = (uint32_t)((c + (int64_t)t * NN) * CB);
+  const uint32_t vo = (uint32_t)((c + (int64_t)t * ZS) * CB);
   auto load_k = [&](int slot, C<T>* k) {
     if constexpr (BUFK) {
       const Buf<T> bk(ks + slot * ks_slot);
@@ -913,7 +911,7 @@ k_zconv_ks(const C<T>* __restrict__ ks, int64_t ks_slot, int n_slots, const C<T>
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     if constexpr (BUF) g[m] = Buf<T>(fg + tile).load(vo, (uint32_t)m * ZST);
-    else g[m] = fg[col + (int64_t)(t + TPL * m) * NN];
+    else g[m] = fg[col + (int64_t)(t + TPL * m) * ZS];
   }
   auto body = [&](int slot, C<T>* v) {
 #pragma unroll
@@ -927,7 +925,7 @@ k_zconv_ks(const C<T>* __restrict__ ks, int64_t ks_slot, int n_slots, const C<T>
     } else {
       C<T>* dst = out + slot * out_slot + col;
 #pragma unroll
-      for (int m = 0; m < E; ++m) dst[(int64_t)(t + TPL * m) * NN] = v[m];
+      for (int m = 0; m < E; ++m) dst[(int64_t)(t + TPL * m) * ZS] = v[m];
     }
   };
   for (int slot = 0; slot < n_slots; ++slot) {
@@ -966,7 +964,7 @@ k_zdual_acc_ks(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
                const C<T>* __restrict__ fg, int first, C<T>* __restrict__ acc_out,
                const C<T>* __restrict__ tw_g) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), H = N / 2;
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   // Shapes of at most 8 elements per thread run lean: the galaxy-kernel sum
   // in registers, stage twiddles from the LDS table, the kernel values loaded
   // after the transform and in two halves, no register prefetch of the next
@@ -985,12 +983,12 @@ k_zdual_acc_ks(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
   twa.init(tw_s, tw_g, t);
   const int kyr = ky <= H ? ky : N - ky, xx = xt * W + c;
   const int64_t col = (int64_t)ky * N + xx;
-  constexpr bool BUF = NN * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
+  constexpr bool BUF = ZS * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr bool BUFK = (int64_t)(H + 1) * (H + 1) * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr uint32_t CB = sizeof(C<T>);
-  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * NN * CB) : 0u;
+  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * ZS * CB) : 0u;
   const int64_t tile = (int64_t)ky * N + xt * W;
-  const uint32_t vo = (uint32_t)((c + (int64_t)t * NN) * CB);
+  const uint32_t vo = (uint32_t)((c + (int64_t)t * ZS) * CB);
   auto load_pi = [&](int slot, bool take, C<T>* v) {
     if constexpr (BUF) {
       const Buf<T> bi(x + slot * x_slot + tile);
@@ -1000,7 +998,7 @@ k_zdual_acc_ks(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
     } else {
 #pragma unroll
       for (int m = 0; m < E; ++m) {
-        const C<T> b = x[slot * x_slot + col + (int64_t)(t + TPL * m) * NN];
+        const C<T> b = x[slot * x_slot + col + (int64_t)(t + TPL * m) * ZS];
         v[m].x = take ? b.x : (T)0;
         v[m].y = take ? b.y : (T)0;
       }
@@ -1066,7 +1064,7 @@ k_zdual_acc_ks(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
   }
 #pragma unroll
   for (int m = 0; m < E; ++m) {
-    const int64_t idx = col + (int64_t)(t + TPL * m) * NN;
+    const int64_t idx = col + (int64_t)(t + TPL * m) * ZS;
     const C<T> g = fg[idx];
     T kgv;
     if constexpr (LEAN) kgv = kg[m];

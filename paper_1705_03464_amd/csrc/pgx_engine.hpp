@@ -227,7 +227,8 @@ template <typename T, int N> struct Engine : EngineBase {
   // so that two blocks share a compute unit)
   static constexpr int WH = W / 2 >= 4 ? W / 2 : W;
   static constexpr int64_t NN = (int64_t)N * N;
-  static constexpr int64_t NC = NN * N;
+  static constexpr int64_t ZS = plane_stride<T, N>();  // plane stride of the working grids
+  static constexpr int64_t NC = ZS * N;                // elements of one
   // second radix schedule of the y passes (autotuner candidate)
   using ShA = typename AltShape<T, N>::type;
   static constexpr int WA =
@@ -1378,7 +1379,7 @@ template <typename T, int N> struct Engine : EngineBase {
         }
         prof.run("bwd_yinv", s, (double)nb * NC * cb + (double)nt * N * cb, [&] {
           k_strided<T, Sh, W, 1, IN_DENSE, OUT_FLAGS><<<dim3(N / W, N, nb), NT, 0, s>>>(
-              x, x, NC, NC, NN, NN, N, N, 0, lflag.as<uint8_t>(), pflag.as<uint8_t>(), NN, fp, twp);
+              x, x, NC, NC, ZS, ZS, N, N, 0, lflag.as<uint8_t>(), pflag.as<uint8_t>(), NN, fp, twp);
           launch_check("yinv(bwd)");
         });
         if (nt > 0) {
@@ -1415,12 +1416,12 @@ template <typename T, int N> struct Engine : EngineBase {
     k_zero_dc<T><<<1, 64, 0, s>>>(A);
     prof.run("bwd_gal_zinv", s, 2.0 * NC * cb, [&] {
       k_strided<T, Sh, W, 1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, 1), NT, 0, s>>>(
-          A, A, 0, 0, N, N, NN, NN, 0, nullptr, nullptr, 0, nullptr, twp);
+          A, A, 0, 0, N, N, ZS, ZS, 0, nullptr, nullptr, 0, nullptr, twp);
       launch_check("gal_zinv");
     });
     prof.run("bwd_gal_yinv", s, 2.0 * NC * cb, [&] {
       k_strided<T, Sh, W, 1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, 1), NT, 0, s>>>(
-          A, A, 0, 0, NN, NN, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
+          A, A, 0, 0, ZS, ZS, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
       launch_check("gal_yinv");
     });
     prof.run("bwd_gal_xgather", s, (double)NC * cb + (double)n_gal * (4 + 4 * sizeof(T)), [&] {
@@ -1483,7 +1484,7 @@ template <typename T, int N> struct Engine : EngineBase {
       });
       prof.run("bwd_dual_ypass", s, 2.0 * nq * NC * cb, [&] {
         k_strided<T, Sh, W, -1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, nq), NT, 0, s>>>(
-            x, x, NC, NC, NN, NN, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
+            x, x, NC, NC, ZS, ZS, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
         launch_check("ypass(dual adjoint)");
       });
       if (ksp) {
@@ -1516,10 +1517,10 @@ template <typename T, int N> struct Engine : EngineBase {
     const uint8_t* pf = pflag.as<uint8_t>();
     if (v == 0)
       k_strided<T, Sh, W, -1, IN_FLAGS, OUT_DENSE><<<dim3(N / W, N, nb), NT, 0, s>>>(
-          x, x, NC, NC, NN, NN, N, N, 0, lf, pf, NN, fp, tw.as<C<T>>());
+          x, x, NC, NC, ZS, ZS, N, N, 0, lf, pf, NN, fp, tw.as<C<T>>());
     else
       k_strided<T, ShA, WA, -1, IN_FLAGS, OUT_DENSE><<<dim3(N / WA, N, nb), NTA, 0, s>>>(
-          x, x, NC, NC, NN, NN, N, N, 0, lf, pf, NN, fp, tw_alt.as<C<T>>());
+          x, x, NC, NC, ZS, ZS, N, N, 0, lf, pf, NN, fp, tw_alt.as<C<T>>());
   }
 
   int pwx() const { return cfg.pw[0]; }
@@ -1650,7 +1651,7 @@ template <typename T, int N> struct Engine : EngineBase {
           k_zconv<T, Sh, W><<<dim3(N / W, N, 1), NT, 0, s>>>(ky, ky_slot, nq, pwz(), fg, x, NC, twp);
           launch_check("zconv(multipoles)");
           k_strided<T, Sh, W, 1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, nq), NT, 0, s>>>(
-              x, x, NC, NC, NN, NN, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
+              x, x, NC, NC, ZS, ZS, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
           launch_check("yinv(multipoles)");
           k_xinv_gather_sweep<T, Sh, YTS><<<dim3((N + YTS - 1) / YTS, kZSeg, nq), (YTS + 1) * TPL, 0, s>>>(
               line_set(), l_p.as<int32_t>(), P, x, NC, N / kZSeg, 2 * q0, RC, gv, twp);
@@ -1737,7 +1738,7 @@ template <typename T, int N> struct Engine : EngineBase {
               line_set(), l_f.as<int32_t>(), cf, F, q0, nq, x, NC, twp, yl, nh, P);
           launch_check("xscatter(multipoles adjoint)");
           k_strided<T, Sh, W, -1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, nq), NT, 0, s>>>(
-              x, x, NC, NC, NN, NN, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
+              x, x, NC, NC, ZS, ZS, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
           launch_check("ypass(multipoles adjoint)");
           k_zdual_acc<T, Sh, W><<<dim3(N / W, N, 1), NT, 0, s>>>(x, NC, nq, ky, ky_slot, pwz(), A, twp);
           launch_check("zacc(multipoles adjoint)");
@@ -1827,7 +1828,7 @@ template <typename T, int N> struct Engine : EngineBase {
       }
       prof.run("dual_yinv", s, 2.0 * nq * NC * cb, [&] {
         k_strided<T, Sh, W, 1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, nq), NT, 0, s>>>(
-            x, x, NC, NC, NN, NN, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
+            x, x, NC, NC, ZS, ZS, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
         launch_check("yinv(dual)");
       });
       if (n_pairs > 0) {
@@ -1880,7 +1881,7 @@ template <typename T, int N> struct Engine : EngineBase {
     });
     prof.run("gal_ypass", s, 2.0 * NC * cb, [&] {
       k_strided<T, Sh, W, -1, IN_DENSE, OUT_DENSE><<<dim3(N / W, N, 1), NT, 0, s>>>(
-          x, x, 0, 0, NN, NN, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
+          x, x, 0, 0, ZS, ZS, N, N, 0, nullptr, nullptr, 0, nullptr, twp);
       launch_check("ypass(gal)");
     });
     prof.run("gal_zpass", s, 2.0 * NC * cb + (double)p1_slot * cb, [&] {

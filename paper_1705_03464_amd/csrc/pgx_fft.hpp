@@ -11,7 +11,7 @@
 
 namespace pgx {
 
-template <typename T> struct C { T x, y; };
+template <typename T> struct alignas(8) C { T x, y; };
 
 template <typename T> __device__ __forceinline__ C<T> cadd(C<T> a, C<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename T> __device__ __forceinline__ C<T> csub(C<T> a, C<T> b) { return {a.x - b.x, a.y - b.y}; }
@@ -156,7 +156,20 @@ template <int N> struct AltShape<double, N> { using type = typename DefaultShape
 constexpr int kPadShift = 4;
 constexpr int kLineExtra = 1;
 __device__ __forceinline__ int lpad(int i) { return i + (i >> kPadShift); }
-template <int N> constexpr int lds_line_elems() { return N + (N >> kPadShift) + kLineExtra; }
+
+// 64-point lines of FP32 grids are transformed in FP64: FP64 arithmetic, stage
+// twiddles and exchange between FP32 loads and stores.  The catalogues of such
+// grids crowd their points into few cells, and the correlations of the tiny
+// candidate set (xi up to 4.4, most of it near 1e-3) sit at the edge of what FP32
+// grids hold: rounding inside the transforms decided whether they met one FP32
+// unit of the largest value (0.5 to 1.3 of it, by the order of the additions
+// alone).  The passes of a 64^3 grid are bound by their launches, so this costs
+// a few per cent there; larger grids would pay with half their occupancy.
+template <typename T, int N> __host__ __device__ constexpr bool fft64() { return sizeof(T) == 4 && N == 64; }
+// LDS entries of one line (of type C<T>; 64-point lines have room for C<double>)
+template <int N> constexpr int lds_line_elems() {
+  return (N == 64 ? 2 : 1) * (N + (N >> kPadShift) + kLineExtra);
+}
 
 // Twiddle providers for stage s >= 1 of butterfly q (j = t + TPL*q), radix
 // index r, k = j mod Ns: exp(-2 pi i r k / (Ns R)).
@@ -190,6 +203,33 @@ template <typename Sh, typename T> struct TwReg {
   }
   template <int s> __device__ __forceinline__ C<T> get(int q, int r, int) const {
     return w[s - 1][q * Sh::radix(s) + r];
+  }
+};
+
+// FP64 twiddles of the 64-point two-stage shapes: (cos, sin) of 2 pi e / 64 for
+// e < 16, the other quadrants by symmetry.
+__device__ static const double kCis64[16][2] = {
+    {1.0, 0.0},
+    {0.99518472667219688624, 0.098017140329560601994},
+    {0.98078528040323044913, 0.1950903220161282678},
+    {0.95694033573220886494, 0.29028467725446236764},
+    {0.92387953251128675613, 0.3826834323650897717},
+    {0.88192126434835502971, 0.47139673682599764856},
+    {0.83146961230254523708, 0.55557023301960222474},
+    {0.77301045336273696081, 0.6343932841636454982},
+    {0.70710678118654752440, 0.70710678118654752440},
+    {0.6343932841636454982, 0.77301045336273696081},
+    {0.55557023301960222474, 0.83146961230254523708},
+    {0.47139673682599764856, 0.88192126434835502971},
+    {0.3826834323650897717, 0.92387953251128675613},
+    {0.29028467725446236764, 0.95694033573220886494},
+    {0.1950903220161282678, 0.98078528040323044913},
+    {0.098017140329560601994, 0.99518472667219688624}};
+struct Tw64 {
+  template <int s> __device__ __forceinline__ C<double> get(int, int r, int k) const {
+    const int e = (r * k) & 63, q = e >> 4;  // exp(-2 pi i e / 64)
+    const double c = kCis64[e & 15][0], d = kCis64[e & 15][1];
+    return q == 0 ? C<double>{c, -d} : q == 1 ? C<double>{-d, -c} : q == 2 ? C<double>{-c, d} : C<double>{d, c};
   }
 };
 
@@ -251,6 +291,16 @@ template <typename Sh> constexpr bool pad_linear() {
 template <typename Sh, int DIR, typename T, typename Sync, typename TW>
 __device__ __forceinline__ void line_fft_tw(C<T>* v, int t, C<T>* line, const TW& tw, Sync sync) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL;
+  if constexpr (fft64<T, N>()) {
+    static_assert(Sh::stages == 2, "Tw64 holds the twiddles of one stage");
+    C<double> d[E];
+#pragma unroll
+    for (int m = 0; m < E; ++m) d[m] = C<double>{(double)v[m].x, (double)v[m].y};
+    line_fft_tw<Sh, DIR, double>(d, t, reinterpret_cast<C<double>*>(line), Tw64{}, sync);
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[m] = C<T>{(T)d[m].x, (T)d[m].y};
+    return;
+  }
   constexpr bool LIN = pad_linear<Sh>();
   // stage 0: inputs j + r*(N/R0) with j = t  ->  v[r] already in place
   stage_compute<Sh, 0, DIR, T, TW>(v, t, tw);

@@ -14,6 +14,7 @@
 
 namespace pgx {
 
+
 // ----------------------------------------------------------------------------
 // Point sets: points sorted by (set, base line), where the base line of a point
 // is z0*N + y0 of its lower CIC corner.  line_start[set*N*N + l] is the first
@@ -30,6 +31,21 @@ template <typename T> struct PointSet {
 
 // Number of lines along each axis of the pruned output window [-w, w].
 __host__ __device__ inline int win_len(int w) { return 2 * w + 1; }
+
+// Elements from one z plane of a working grid (the batch slots, the galaxy
+// spectrum, the adjoint accumulator, kept spectra) to the next.  A z column
+// of a dense power-of-two grid has every element N N 8 bytes after the last,
+// all on the same few memory channels; 16 elements (one 128-byte line) more
+// per plane spread it over all of them.  ms per launch, dense and padded: the
+// 1024^3 cross-power pass 29.4 and 20.5, the 512^3 dual-form passes (10 slots)
+// 4.20 and 3.53 (k_zconv_ks), 4.23 and 3.50 (k_zdual_acc_ks), the galaxy pass
+// 0.60 and 0.48, at 256^3 0.51 and 0.48.  Any odd number of lines does the
+// same; 4 KB is worse (256^3: 0.61).  Smaller grids stay in the caches.  The
+// y passes are as fast either way.  The window buffers and the FP64 plain
+// grids are dense.
+template <typename T, int N> __host__ __device__ constexpr int64_t plane_stride() {
+  return (int64_t)N * N + (std::is_same<T, float>::value && N >= 256 ? 16 : 0);
+}
 
 // Block size helpers
 template <typename Sh, int W> struct Blk {
@@ -342,12 +358,12 @@ __device__ __forceinline__ void task_source(const int32_t* __restrict__ tasks, i
   s = line_start[key];
   e = line_start[key + 1];
 }
-// y and z weight of a point of source q on its line
-template <typename T, bool TSC> __device__ __forceinline__ T source_weight(int q, T fy, T fz, int N) {
+// w times the y and z weight of a point of source q on its line
+template <typename T, bool TSC> __device__ __forceinline__ T source_weight(T w, int q, T fy, T fz, int N) {
   if constexpr (TSC)
-    return tsc_line_weight<T>((q & 3) - 2, fy, 0, N) * tsc_line_weight<T>((q >> 2) - 2, fz, 0, N);
+    return w * tsc_line_weight<T>((q & 3) - 2, fy, 0, N) * tsc_line_weight<T>((q >> 2) - 2, fz, 0, N);
   else
-    return ((q & 1) ? fy : (T)1 - fy) * ((q & 2) ? fz : (T)1 - fz);
+    return w * ((q & 1) ? fy : (T)1 - fy) * ((q & 2) ? fz : (T)1 - fz);
 }
 
 // ----------------------------------------------------------------------------
@@ -361,6 +377,8 @@ template <typename T, bool TSC> __device__ __forceinline__ T source_weight(int q
 // node (clustered catalogues put many points on one node, and same-address
 // LDS atomics serialise), and only the last point of each run adds to the
 // line.  The next trip's points are in flight during the current one.
+// 64^3 lines hold FP64 (fft64): there the additions are FP64 ones, each point's
+// own (47 us per forward of the candidate set with run sums, 38 without).
 // ----------------------------------------------------------------------------
 template <typename T, typename Sh, int W, bool TSC = false>
 static __global__ void __launch_bounds__(W * Sh::TPL)
@@ -371,6 +389,8 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
   constexpr int NT = W * TPL, NB = line_sources<TSC>(), NX = TSC ? 3 : 2;
   constexpr int LW = 64 / TPL, NR = LW * 2 * NB;  // lines and sources of a wavefront
+  // additions to a node: at 64^3 in FP64 (the lines hold FP64 there)
+  typedef typename std::conditional<fft64<T, N>(), double, T>::type A;
   constexpr int64_t NN = (int64_t)N * N;
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W * LL];
@@ -383,8 +403,9 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
   const int task = block_task<N, W>(l, rev);
   const bool active = task < n_tasks;
   C<T>* line = lines + l * LL;
+  C<A>* sums = reinterpret_cast<C<A>*>(line);
 #pragma unroll
-  for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
+  for (int m = 0; m < E; ++m) sums[lpad(t + TPL * m)] = C<A>{0, 0};
   const int32_t word = active ? tasks[task] : 0;
   const int slot = (int)(word / NN);
   const int li = (int)(word - (int64_t)slot * NN);
@@ -421,7 +442,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
     const Point nx = fetch(base + 64 + lane);
     const bool ok = a.r >= 0;
     const int r = ok ? a.r : 0, q = r % NB, lp = 2 * l0 + r / NB;  // lp = 2 line + part
-    const T w = a.wt * a.sc * source_weight<T, TSC>(q, a.fy, a.fz, N);
+    const T w = source_weight<T, TSC>(a.wt * a.sc, q, a.fy, a.fz, N);
     T wx[NX];
     int lo = a.x0;
     if constexpr (TSC) {
@@ -430,24 +451,45 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
       wx[0] = (T)1 - a.fx;
       wx[1] = a.fx;
     }
-    SegRuns runs;
-    runs.init(ok ? r * N + ((lo + NX - 2) & (N - 1)) : -1 - lane);
-    T* dst = reinterpret_cast<T*>(lines + (lp >> 1) * LL) + (lp & 1);
+    A* dst = reinterpret_cast<A*>(lines + (lp >> 1) * LL) + (lp & 1);
+    if constexpr (std::is_same<A, T>::value) {
+      SegRuns runs;
+      runs.init(ok ? r * N + ((lo + NX - 2) & (N - 1)) : -1 - lane);
+      T v[NX];
 #pragma unroll
-    for (int j = 0; j < NX; ++j) {
-      const T v = runs.add(w * wx[j]);
-      if (ok && runs.tail) atomicAdd(dst + 2 * lpad((lo + j) & (N - 1)), v);
+      for (int j = 0; j < NX; ++j) v[j] = runs.add(w * wx[j]);
+      bool left = ok && runs.tail;
+      if constexpr (LW == 1) {
+        // one source after another, as when each is a trip of its own
+        for (uint64_t m = __ballot(left); m != 0; m = __ballot(left)) {
+          const int turn = __builtin_amdgcn_readlane(r, (int)__builtin_ctzll(m));
+          if (left && r == turn) {
+#pragma unroll
+            for (int j = 0; j < NX; ++j) atomicAdd(dst + 2 * lpad((lo + j) & (N - 1)), v[j]);
+            left = false;
+          }
+        }
+      } else if (left) {
+#pragma unroll
+        for (int j = 0; j < NX; ++j) atomicAdd(dst + 2 * lpad((lo + j) & (N - 1)), v[j]);
+      }
+    } else if (ok) {
+#pragma unroll
+      for (int j = 0; j < NX; ++j) atomicAdd(dst + 2 * lpad((lo + j) & (N - 1)), (A)w * (A)wx[j]);
     }
     a = nx;
   }
   wave_sync();  // a line belongs to one wavefront
   C<T> v[E];
 #pragma unroll
-  for (int m = 0; m < E; ++m) v[m] = line[lpad(t + TPL * m)];
+  for (int m = 0; m < E; ++m) {
+    const C<A> a = sums[lpad(t + TPL * m)];
+    v[m] = C<T>{(T)a.x, (T)a.y};
+  }
   wave_sync();
   line_fft<Sh, -1>(v, t, line, tw_s, wave_sync);
   if (active) {
-    C<T>* o = out + (int64_t)slot * NN * N + (int64_t)li * N;
+    C<T>* o = out + ((int64_t)slot * N + li / N) * plane_stride<T, N>() + (int64_t)(li % N) * N;
 #pragma unroll
     for (int m = 0; m < E; ++m) o[t + TPL * m] = v[m];
   }
@@ -600,47 +642,65 @@ k_strided(const C<T>* in, C<T>* out, int64_t in_slot, int64_t out_slot,
 // to zero, the spectrum is stored to `fg_out`, and the product is |Fg|^2.
 // STORE mode also writes each pair-field spectrum (after the forward z
 // transform) to `spec` at its field-pair index, for the adjoint.
+// Lines of 16 elements per thread (1024^3) cannot hold the next slot's columns
+// beside G and the transform; they are held to 128 VGPRs instead, so that two
+// blocks share a compute unit (18.5 ms per 4-slot launch, with 68 registers
+// spilled; 20.5 with one block and no spills, 20.7 with one block and the
+// next slot's columns in flight).  The galaxy's pass, one slot, spills more
+// than that gives (7.2 ms with one block, 10.9 with two).
 // ----------------------------------------------------------------------------
 template <typename T, typename Sh, int W, bool GAL, bool STORE = false, bool TWREG = kZTwReg>
-static __global__ void __launch_bounds__(W * Sh::TPL, GAL && !TWREG && Sh::E <= 8 ? 8 : 1)
+static __global__ void __launch_bounds__(W * Sh::TPL, Sh::E > 8 ? (GAL ? 1 : 4) : GAL && !TWREG ? 8 : 1)
 k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
          const int32_t* __restrict__ slot_fp, int n_slots, const C<T>* __restrict__ fg,
          C<T>* __restrict__ fg_out, C<T>* __restrict__ out, int64_t out_slot, int pw,
          const C<T>* __restrict__ tw_g, C<T>* __restrict__ spec = nullptr) {
   constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
-  constexpr int64_t NN = (int64_t)N * N;
+  constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   // slot pipeline when a thread has room for a second set of columns
   constexpr bool PIPE = !GAL && E <= 8;
   __shared__ C<T> tw_s[tw_lds_entries<Sh, TWREG>()];
   __shared__ C<T> lines[W][LL];
-  __shared__ uint32_t pmask[GAL ? 1 : kMaxSlots][TPL];
+  // plane masks of the slots: bit m of pmask[s][t] = plane t + TPL m of slot s
+  // holds data; of MSLOTS slots at a time where LDS decides the occupancy
+  constexpr int MSLOTS = E > 8 ? 16 : kMaxSlots;
+  typedef typename std::conditional<(E > 8), uint16_t, uint32_t>::type mask_t;
+  __shared__ mask_t pmask[GAL ? 1 : MSLOTS][TPL];
   int xt = blockIdx.x, ky = blockIdx.y;
   if constexpr (narrow_tile<T, W>()) xcd_tile(xt, ky);
   const int c = threadIdx.x % W, t = threadIdx.x / W;
   TwAuto<Sh, T, TWREG> twa;
   twa.init(tw_s, tw_g, t);
-  if constexpr (!GAL) {
-    // plane masks of the batch: bit m of pmask[s][t] = plane t + TPL m of
-    // slot s holds data
-    for (int i = threadIdx.x; i < n_slots * TPL; i += W * TPL) {
+  auto stage_masks = [&](int s0) {
+    const int ns = n_slots - s0 < MSLOTS ? n_slots - s0 : MSLOTS;
+    for (int i = threadIdx.x; i < ns * TPL; i += W * TPL) {
       const int s = i / TPL, tt = i - s * TPL;
-      const uint8_t* pf = pflag + (int64_t)slot_fp[s] * N + tt;
+      const uint8_t* pf = pflag + (int64_t)slot_fp[s0 + s] * N + tt;
       uint32_t mk = 0;
 #pragma unroll
       for (int m = 0; m < E; ++m) mk |= (uint32_t)(pf[TPL * m] != 0) << m;
-      pmask[s][tt] = mk;
+      pmask[s][tt] = (mask_t)mk;
     }
     block_sync();
-  }
+  };
+  if constexpr (!GAL) stage_masks(0);
   const int64_t col = (int64_t)ky * N + xt * W + c;
   // buffer path (fields up to 2 GiB per slot): tile base in a scalar resource,
   // per-lane offset of the column, per-element scalar offset of the z plane
-  constexpr bool BUF = NN * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
+  constexpr bool BUF = ZS * N * (int64_t)sizeof(C<T>) < ((int64_t)1 << 31);
   constexpr uint32_t CB = sizeof(C<T>);
-  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * NN * CB) : 0u;  // TPL planes
+  constexpr uint32_t ZST = BUF ? (uint32_t)(TPL * ZS * CB) : 0u;  // TPL planes
   const int64_t tile = (int64_t)ky * N + xt * W;
-  const uint32_t vo = (uint32_t)((c + (int64_t)t * NN) * CB);
+  const uint32_t vo = (uint32_t)((c + (int64_t)t * ZS) * CB);
   const int pw2 = 2 * pw + 1;
+  // larger fields: a scalar base per group of TPL planes (uniform over the
+  // block) plus a 32-bit lane offset
+  constexpr int64_t ZG = (int64_t)TPL * ZS;
+  auto at = [&](auto* base, uint32_t off) {
+    typedef typename std::remove_pointer<decltype(base)>::type V;
+    typedef typename std::conditional<std::is_const<V>::value, const char, char>::type B;
+    return reinterpret_cast<V*>(reinterpret_cast<B*>(base) + off);
+  };
   // columns of one slot; absent planes are zero (buffer path: out-of-range
   // offset; pointer path: the tile's first element is read and zeroed when
   // the columns are taken)
@@ -650,20 +710,20 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
 #pragma unroll
       for (int m = 0; m < E; ++m) dst[m] = bi.load(vo, (uint32_t)m * ZST);
     } else if constexpr (GAL) {
-      const C<T>* src = in + slot * in_slot + col;
+      const C<T>* src = in + slot * in_slot + tile;
 #pragma unroll
-      for (int m = 0; m < E; ++m) dst[m] = src[(int64_t)(t + TPL * m) * NN];
+      for (int m = 0; m < E; ++m) dst[m] = *at(src + m * ZG, vo);
     } else if constexpr (BUF) {
-      const uint32_t mk = take ? pmask[slot][t] : 0u;
+      const uint32_t mk = take ? pmask[slot % MSLOTS][t] : 0u;
       const Buf<T> bi(in + slot * in_slot + tile);
 #pragma unroll
       for (int m = 0; m < E; ++m)
         dst[m] = bi.load((mk >> m) & 1u ? vo + (uint32_t)m * ZST : kBufOff, 0u);
     } else {
-      const uint32_t mk = take ? pmask[slot][t] : 0u;
-      const C<T>* src = in + slot * in_slot + col;
+      const uint32_t mk = take ? pmask[slot % MSLOTS][t] : 0u;
+      const C<T>* src = in + slot * in_slot + tile;
 #pragma unroll
-      for (int m = 0; m < E; ++m) dst[m] = src[(mk >> m) & 1u ? (int64_t)(t + TPL * m) * NN : 0];
+      for (int m = 0; m < E; ++m) dst[m] = *at(src + m * ZG, (mk >> m) & 1u ? vo : 0u);
     }
   };
   auto take_cols = [&](int slot, const C<T>* cur, C<T>* v) {
@@ -671,7 +731,7 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
 #pragma unroll
       for (int m = 0; m < E; ++m) v[m] = cur[m];
     } else {
-      const uint32_t mk = pmask[slot][t];
+      const uint32_t mk = pmask[slot % MSLOTS][t];
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         const bool ok = (mk >> m) & 1u;
@@ -692,7 +752,7 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
       for (int m = 0; m < E; ++m) g[m] = bg.load(vo, (uint32_t)m * ZST);
     } else {
 #pragma unroll
-      for (int m = 0; m < E; ++m) g[m] = fg[col + (int64_t)(t + TPL * m) * NN];
+      for (int m = 0; m < E; ++m) g[m] = *at(fg + tile + m * ZG, vo);
     }
   }
   auto body = [&](int slot, C<T>* v) {
@@ -706,7 +766,7 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
         for (int m = 0; m < E; ++m) bs.store(v[m], vo, (uint32_t)m * ZST);
       } else {
 #pragma unroll
-        for (int m = 0; m < E; ++m) fg_out[col + (int64_t)(t + TPL * m) * NN] = v[m];
+        for (int m = 0; m < E; ++m) *at(fg_out + tile + m * ZG, vo) = v[m];
       }
 #pragma unroll
       for (int m = 0; m < E; ++m) v[m] = C<T>{v[m].x * v[m].x + v[m].y * v[m].y, (T)0};
@@ -714,14 +774,14 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
       if constexpr (STORE) {
         // keep the pair-field spectrum (field pair slot_fp[slot], dense N^3)
         // for the adjoint
-        C<T>* sp = spec + (int64_t)slot_fp[slot] * (NN * N);
+        C<T>* sp = spec + (int64_t)slot_fp[slot] * (ZS * N);
         if constexpr (BUF) {
           const Buf<T> bs(sp + tile);
 #pragma unroll
           for (int m = 0; m < E; ++m) bs.store(v[m], vo, (uint32_t)m * ZST);
         } else {
 #pragma unroll
-          for (int m = 0; m < E; ++m) sp[col + (int64_t)(t + TPL * m) * NN] = v[m];
+          for (int m = 0; m < E; ++m) *at(sp + tile + m * ZG, vo) = v[m];
         }
       }
 #pragma unroll
@@ -738,7 +798,8 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
         bo.store(v[m], pz < pw2 ? (uint32_t)((c + (int64_t)pz * NN) * CB) : kBufOff, 0u);
       }
     } else {
-      C<T>* dst = out + slot * out_slot + col;
+      // (a lane offset may exceed 4 GiB when the window is wide)
+      C<T>* dst = out + slot * out_slot + tile + c;
 #pragma unroll
       for (int m = 0; m < E; ++m) {
         const int pz = (t + TPL * m + pw) & (N - 1);
@@ -770,6 +831,12 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
     if (slot < n_slots) trip(slot, ca, cb);
   } else {
     for (int slot = 0; slot < n_slots; ++slot) {
+      if constexpr (!GAL) {
+        if (slot > 0 && slot % MSLOTS == 0) {
+          block_sync();
+          stage_masks(slot);
+        }
+      }
       if (slot > 0) load_cols(slot, true, ca);
       C<T> v[E];
       take_cols(slot, ca, v);

@@ -368,9 +368,12 @@ static __global__ void k_dual_reduce(const int32_t* __restrict__ line_start, int
 // line-major order of the pair catalogue: sort key (base line, x0) of each
 // pair, so that within a base line the points run in x order
 static __global__ void k_line_x_key(const int32_t* __restrict__ key, const int32_t* __restrict__ x0,
-                                    int64_t P, int64_t nn, int n, int32_t* __restrict__ out) {
+                                    int64_t P, int64_t nn, int n, int32_t* __restrict__ out,
+                                    int32_t* __restrict__ place) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < P) out[p] = (int32_t)((key[p] % nn) * n + x0[p]);
+  if (p >= P) return;
+  out[p] = (int32_t)((key[p] % nn) * n + x0[p]);
+  place[p] = (int32_t)p;
 }
 // TSC plans: the sort key (nearest-node line, nearest x node) of each pair,
 // from its CIC corner and fractions (the same FP32 fractions, and the same
@@ -379,25 +382,31 @@ template <typename T>
 static __global__ void k_line_x_key_tsc(const int32_t* __restrict__ key, const int32_t* __restrict__ x0,
                                         const T* __restrict__ fx, const T* __restrict__ fy,
                                         const T* __restrict__ fz, int64_t P, int64_t nn, int n,
-                                        int32_t* __restrict__ out) {
+                                        int32_t* __restrict__ out, int32_t* __restrict__ place) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= P) return;
   const int line = (int)(key[p] % nn);
   const int cy = tsc_nearest(line % n, fy[p], n), cz = tsc_nearest(line / n, fz[p], n);
   const int cx = tsc_nearest(x0[p], fx[p], n);
   out[p] = (int32_t)(((int64_t)cz * n + cy) * n + cx);
+  place[p] = (int32_t)p;
 }
-// base line of a sorted (line, x0) key
-static __global__ void k_key_line(const int32_t* __restrict__ k, int64_t P, int n,
-                                  int32_t* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < P) out[i] = k[i] / n;
-}
-// field of each pair in line-major order (lp: line-major -> field-major index)
-static __global__ void k_field_of(const int32_t* __restrict__ lp, const int32_t* __restrict__ key,
-                                  int64_t P, int64_t nn, int32_t* __restrict__ out) {
+// the pairs in line-major order (lp: line-major -> field-major index): point
+// records and field
+template <typename T>
+static __global__ void k_line_records(const int32_t* __restrict__ lp, const int32_t* __restrict__ key,
+                                      const int32_t* __restrict__ x0, const T* __restrict__ fx,
+                                      const T* __restrict__ fy, const T* __restrict__ fz, int64_t P, int64_t nn,
+                                      int32_t* __restrict__ ox0, T* __restrict__ ofx, T* __restrict__ ofy,
+                                      T* __restrict__ ofz, int32_t* __restrict__ field) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < P) out[k] = (int32_t)(key[lp[k]] / nn);
+  if (k >= P) return;
+  const int32_t p = lp[k];
+  ox0[k] = x0[p];
+  ofx[k] = fx[p];
+  ofy[k] = fy[p];
+  ofz[k] = fz[p];
+  field[k] = (int32_t)(key[p] / nn);
 }
 
 // Scatter coefficients of the bin pairs: coef[q*F + f] = (a_f,b1 / s_b1,

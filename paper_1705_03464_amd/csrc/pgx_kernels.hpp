@@ -500,6 +500,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
 // N*N for z) over tiles of W adjacent x positions.  Tile (xt, a): column base
 // a*A + xt*W.  Input modes:
 //   IN_DENSE   every element read;
+//   IN_NO_MEAN every element read, the first of the field (its k = 0 mode) as 0;
 //   IN_FLAGS   element e counts only when lflag[a*N + e] != 0, and the whole
 //              tile is skipped when pflag[a] == 0 (a field written sparsely by
 //              the x pass; its untouched elements hold stale data);
@@ -513,7 +514,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
 //              skipped when pflag[a] == 0).
 // Batched over blockIdx.z with per-slot strides; flags per field pair slot_fp.
 // ----------------------------------------------------------------------------
-enum { IN_DENSE = 0, IN_FLAGS = 1, IN_WINDOW = 2 };
+enum { IN_DENSE = 0, IN_FLAGS = 1, IN_WINDOW = 2, IN_NO_MEAN = 3 };
 enum { OUT_DENSE = 0, OUT_WINDOW = 1, OUT_FLAGS = 2 };
 
 template <typename T, typename Sh, int W, int DIR, int IN, int OUT>
@@ -595,6 +596,9 @@ k_strided(const C<T>* in, C<T>* out, int64_t in_slot, int64_t out_slot,
 #pragma unroll
       for (int m = 0; m < E; ++m) v[m] = src[(int64_t)(t + TPL * m) * in_es];
     }
+  }
+  if constexpr (IN == IN_NO_MEAN) {
+    if (xt == 0 && a == 0 && threadIdx.x == 0) v[0] = C<T>{0, 0};
   }
   block_sync();
   twa.template fft<DIR>(v, t, lines[c]);

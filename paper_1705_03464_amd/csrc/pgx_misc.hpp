@@ -1,6 +1,8 @@
 // Smaller kernels: weights, deterministic FP64 reductions, the finalisation
 // formulas, and the pieces of the plain one-field-at-a-time path.
 #pragma once
+#include "pgx_pairs.hpp"
+
 #include "pgx_host.hpp"
 #include "pgx_kernels.hpp"
 
@@ -18,28 +20,20 @@ static __global__ void k_fill_value(V* __restrict__ p, int64_t n, V v) {
     p[i] = v;
 }
 
-// fs[f] = first index of the sorted keys with key >= f nn, for f in [0, F]
-// (binary search; the field boundaries of a field-major catalogue)
+// Field boundaries of a field-major catalogue: fs[f] = first index of the sorted
+// keys with key >= f nn, f in [0, F], and the fields' counts, to the caller's
+// array (when given) and to host memory.
 static __global__ void k_field_starts(const int32_t* __restrict__ key, int64_t n, int64_t nn, int F,
-                                      int32_t* __restrict__ fs) {
+                                      int32_t* __restrict__ fs, int64_t* __restrict__ counts,
+                                      int64_t* __restrict__ host_counts) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f > F) return;
-  const int64_t t = (int64_t)f * nn;
-  int64_t lo = 0, hi = n;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if ((int64_t)key[mid] < t)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  fs[f] = (int32_t)lo;
-}
-
-static __global__ void k_field_counts(const int32_t* __restrict__ line_start, int64_t nn, int F,
-                               int64_t* __restrict__ counts) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f < F) counts[f] = (int64_t)line_start[(int64_t)(f + 1) * nn] - line_start[(int64_t)f * nn];
+  const int64_t a = lower_bound_key(key, n, (int64_t)f * nn);
+  fs[f] = (int32_t)a;
+  if (f == F) return;
+  const int64_t c = lower_bound_key(key, n, (int64_t)(f + 1) * nn) - a;
+  if (counts) counts[f] = c;
+  host_counts[f] = c;
 }
 
 static __global__ void k_export_pairs(const int32_t* __restrict__ key, const int32_t* __restrict__ pi,
@@ -52,12 +46,31 @@ static __global__ void k_export_pairs(const int32_t* __restrict__ key, const int
   if (j) j[p] = pj[p];
 }
 
-// weights must be finite and >= 0
-static __global__ void k_validate_w(const float* __restrict__ w, int64_t n, int* __restrict__ err) {
+// weights must be finite and >= 0 (err: a word of host memory)
+static __global__ void k_validate_w(const float* __restrict__ w, int64_t n, int* err) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const float v = w[i];
-  if (!isfinite(v) || v < 0.0f) atomicOr(err, 4);
+  if (!isfinite(v) || v < 0.0f) raise_flag(err);
+}
+
+// up to five arrays (any of them absent) one after another
+struct CopyList {
+  const double* src[5];
+  int64_t len[5];
+};
+static __global__ void k_copy_list(CopyList c, double* __restrict__ dst) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double* d = dst;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    if (i < c.len[k]) {
+      if (c.src[k]) d[i] = c.src[k][i];
+      return;
+    }
+    i -= c.len[k];
+    d += c.len[k];
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -269,6 +282,7 @@ struct FinalizeArgs {
   double* xi_dp;
   double* b_pg;
   double* q_eff;
+  double* wsum_out;      // copy of wsum, or null
 };
 
 __device__ __forceinline__ double q_estimator(double b, double x, double xw, int mode) {
@@ -280,6 +294,7 @@ static __global__ void k_finalize(FinalizeArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const double wg = a.wg[0];
   if (i < a.R) a.xi_gg[i] = a.Sgg[i] / (a.nb[i] * wg * wg);
+  if (i < a.F && a.wsum_out) a.wsum_out[i] = a.wsum[i];
   if (i < a.F) a.xi_dp[i] = 2.0 * a.wsum[i] * a.L * a.L * a.L / (wg * wg * a.vol[i]) - 1.0;
   if (i >= a.F * a.R) return;
   const int f = i / a.R, b = i % a.R;

@@ -70,33 +70,39 @@ __device__ __forceinline__ void cic_of(double x, double gscale, int N, int& i0, 
   i0 = ((int)fl) & (N - 1);
 }
 
-// validation: bit 1 non-finite position, bit 2 outside [0, L), bit 4 bad weight
-static __global__ void k_validate(const double* __restrict__ x, const double* __restrict__ y,
-                           const double* __restrict__ z, const float* __restrict__ w, int64_t n,
-                           double L, int* __restrict__ err) {
+// Validation of a catalogue (err, three words of host memory that the host has
+// cleared: non-finite position, position outside [0, L), bad weight; plain
+// stores, as the lanes that write one all write 1), the cell of each galaxy and
+// the positions kept for the multipoles, one pass.  Rejected positions are dealt
+// out over the cells, so that the pair count that still runs over them is no
+// longer than a uniform catalogue's.
+__device__ __forceinline__ void raise_flag(int* f) {
+  __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+static __global__ void k_ingest(const double* __restrict__ x, const double* __restrict__ y,
+                                const double* __restrict__ z, const float* __restrict__ w, int64_t n, double L,
+                                double side, int nc, int32_t* __restrict__ key, int32_t* __restrict__ idx,
+                                double* __restrict__ kx, double* __restrict__ ky, double* __restrict__ kz,
+                                int* err) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  int e = 0;
   const double a = x[i], b = y[i], c = z[i];
-  if (!isfinite(a) || !isfinite(b) || !isfinite(c)) e |= 1;
-  else if (a < 0.0 || a >= L || b < 0.0 || b >= L || c < 0.0 || c >= L) e |= 2;
+  const bool finite = isfinite(a) && isfinite(b) && isfinite(c);
+  const bool ok = finite && a >= 0.0 && a < L && b >= 0.0 && b < L && c >= 0.0 && c < L;
+  if (!ok) raise_flag(err + (finite ? 1 : 0));
   if (w) {
     const float v = w[i];
-    if (!isfinite(v) || v < 0.0f) e |= 4;
+    if (!isfinite(v) || v < 0.0f) raise_flag(err + 2);
   }
-  if (e) atomicOr(err, e);
-}
-
-static __global__ void k_cell_keys(const double* __restrict__ x, const double* __restrict__ y,
-                            const double* __restrict__ z, int64_t n, double side, int nc,
-                            int32_t* __restrict__ key, int32_t* __restrict__ idx) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int cx = min((int)(x[i] / side), nc - 1);
-  int cy = min((int)(y[i] / side), nc - 1);
-  int cz = min((int)(z[i] / side), nc - 1);
-  key[i] = (cx * nc + cy) * nc + cz;
+  const int ncell = nc * nc * nc;
+  const int cx = ok ? min((int)(a / side), nc - 1) : 0;
+  const int cy = ok ? min((int)(b / side), nc - 1) : 0;
+  const int cz = ok ? min((int)(c / side), nc - 1) : 0;
+  key[i] = ok ? (cx * nc + cy) * nc + cz : (int)(i % ncell);
   idx[i] = (int32_t)i;
+  kx[i] = a;
+  ky[i] = b;
+  kz[i] = c;
 }
 
 static __global__ void k_gather_pos(const int32_t* __restrict__ perm, const double* __restrict__ x,
@@ -110,21 +116,26 @@ static __global__ void k_gather_pos(const int32_t* __restrict__ perm, const doub
   pz[p] = z[i];
 }
 
-// Counts of sorted keys (n < 2^31): only the ends of each run of equal keys
-// touch the histogram (the first adds -p, the last p + 1), so equal keys do
-// not contend for one address.
-static __global__ void k_run_counts(const int32_t* __restrict__ key, int64_t n, int32_t* __restrict__ h) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const int32_t k = key[p];
-  const bool first = p == 0 || key[p - 1] != k;
-  const bool last = p == n - 1 || key[p + 1] != k;
-  if (first && last)
-    atomicAdd(&h[k], 1);
-  else if (first)
-    atomicAdd(&h[k], -(int32_t)p);
-  else if (last)
-    atomicAdd(&h[k], (int32_t)(p + 1));
+// first index of the sorted keys with key >= t (binary search)
+__device__ __forceinline__ int64_t lower_bound_key(const int32_t* __restrict__ key, int64_t n, int64_t t) {
+  int64_t lo = 0, hi = n;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)key[mid] < t)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+// starts[k] = first index of the sorted keys with key >= k div, for k in [0, nkeys].
+// A search per entry: neighbouring lanes walk the same upper levels, and one
+// launch takes the place of a fill, a histogram and a two-launch scan, however
+// the keys are spread.
+static __global__ void k_starts(const int32_t* __restrict__ key, int64_t n, int32_t div, int64_t nkeys,
+                                int32_t* __restrict__ starts) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k <= nkeys) starts[k] = (int32_t)lower_bound_key(key, n, k * div);
 }
 
 // One wavefront per galaxy p (in cell order); its candidates are the galaxies
@@ -135,9 +146,10 @@ static __global__ void k_run_counts(const int32_t* __restrict__ key, int64_t n, 
 // below it), so a galaxy's pairs are written contiguously and in list order
 // (coalesced stores, and the same order as a serial loop over the list).
 // COUNT: cnt[p] = number of kept pairs.  EMIT: pairs written at off[p] + rank:
-// the sort key (field, base line of the midpoint) and the catalogue indices
-// i < j only; the midpoint's CIC corner and fractions are recomputed after
-// the sort by k_pair_cic, with coalesced stores.
+// the sort key (field, base line of the midpoint), the catalogue indices i < j
+// and the place itself (the value the sort carries along) only; the midpoint's
+// CIC corner and fractions are recomputed after the sort by k_pair_cic, with
+// coalesced stores.
 constexpr int kPairWaves = 4;  // wavefronts per block
 template <bool EMIT, typename T>
 static __global__ void __launch_bounds__(64 * kPairWaves)
@@ -145,12 +157,13 @@ k_pairs(PairCfg c, const double* __restrict__ px, const double* __restrict__ py,
         const double* __restrict__ pz, const int32_t* __restrict__ perm,
         const int32_t* __restrict__ cell_of, const int32_t* __restrict__ cell_start, int64_t n,
         int64_t* __restrict__ cnt_off, int32_t* __restrict__ skey, int32_t* __restrict__ oi,
-        int32_t* __restrict__ oj) {
+        int32_t* __restrict__ oj, int32_t* __restrict__ place) {
 #pragma clang fp contract(off)
   const int lane = (int)(threadIdx.x & 63);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const int64_t NN = (int64_t)c.N * c.N;
   const int nc = c.nc;
+  if (!EMIT && blockIdx.x == 0 && threadIdx.x == 0) cnt_off[n] = 0;  // a scan over n + 1 ends with the total
   for (int64_t p = (int64_t)blockIdx.x * kPairWaves + (threadIdx.x >> 6); p < n;
        p += (int64_t)gridDim.x * kPairWaves) {
     const int cell = cell_of[p];
@@ -222,6 +235,7 @@ k_pairs(PairCfg c, const double* __restrict__ px, const double* __restrict__ py,
         skey[at] = okey;
         oi[at] = oa;
         oj[at] = ob;
+        place[at] = (int32_t)at;
       }
       w += __popcll(kept);
     }
@@ -298,6 +312,22 @@ static __global__ void k_gather(const int32_t* __restrict__ perm, const V* __res
   if (p >= n) return;
   dst[p] = src[perm[p]];
 }
+// point records in sorted order (perm kept as idx)
+template <typename T>
+static __global__ void k_gather_points(const int32_t* __restrict__ perm, const int32_t* __restrict__ x0,
+                                       const T* __restrict__ fx, const T* __restrict__ fy,
+                                       const T* __restrict__ fz, int64_t n, int32_t* __restrict__ idx,
+                                       int32_t* __restrict__ ox0, T* __restrict__ ofx, T* __restrict__ ofy,
+                                       T* __restrict__ ofz) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  const int32_t q = perm[p];
+  idx[p] = q;
+  ox0[p] = x0[q];
+  ofx[p] = fx[q];
+  ofy[p] = fy[q];
+  ofz[p] = fz[q];
+}
 
 // mark the (up to) four lines a point's CIC footprint touches, for the field
 // pair of its field (fp = field / 2)
@@ -318,16 +348,26 @@ static __global__ void k_mark_lines(const int32_t* __restrict__ skey, int64_t n,
       fl[(int64_t)((z0 + dz) & (N - 1)) * N + ((y0 + dy) & (N - 1))] = 1;
 }
 
-// plane flag = any line of the plane non-empty
+// plane flag = any line of the plane non-empty; one wavefront per plane
 static __global__ void k_plane_flags(const uint8_t* __restrict__ flags, int N, int64_t n_planes,
                               uint8_t* __restrict__ pflags) {
-  const int64_t pl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t pl = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (pl >= n_planes) return;
+  const int lane = (int)(threadIdx.x & 63u);
   const uint8_t* f = flags + pl * N;
   int any = 0;
-  for (int y = 0; y < N; ++y) any |= f[y];
-  pflags[pl] = (uint8_t)(any ? 1 : 0);
+  for (int y = lane; y < N; y += 64) any |= f[y];
+  const uint64_t m = __ballot(any != 0);
+  if (lane == 0) pflags[pl] = (uint8_t)(m != 0 ? 1 : 0);
 }
+// out[k] (host memory) = pos[min(k batch, n_fp) nn], k in [0, n]: the first x-pass
+// task of each batch, and their number
+static __global__ void k_batch_offsets(const int32_t* __restrict__ pos, int n, int batch, int n_fp, int64_t nn,
+                                       int32_t* __restrict__ out) {
+  for (int k = threadIdx.x; k <= n; k += blockDim.x) out[k] = pos[(int64_t)min(k * batch, n_fp) * nn];
+}
+// host copy of one count
+static __global__ void k_publish(const int64_t* __restrict__ v, int64_t* __restrict__ out) { out[0] = v[0]; }
 
 // task words for the x pass: slot * N^2 + line, slot = fp % batch
 static __global__ void k_emit_tasks(const uint8_t* __restrict__ flags, const int32_t* __restrict__ pos,
@@ -337,11 +377,6 @@ static __global__ void k_emit_tasks(const uint8_t* __restrict__ flags, const int
   const int64_t NN = (int64_t)N * N;
   const int64_t fp = i / NN, l = i % NN;
   tasks[pos[i]] = (int32_t)((fp % batch) * NN + l);
-}
-
-static __global__ void k_iota(int32_t* __restrict__ a, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = (int32_t)i;
 }
 
 }  // namespace pgx

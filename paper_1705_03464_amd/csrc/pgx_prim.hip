@@ -33,15 +33,6 @@ void exscan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t s, DBuf&
   PGX_HIP(rocprim::exclusive_scan(t, bytes, in, out, (int64_t)0, (size_t)n, rocprim::plus<int64_t>(), s));
 }
 
-void exscan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t s, DBuf& tmp) {
-  if (n <= 0) return;
-  size_t bytes = 0;
-  PGX_HIP(rocprim::exclusive_scan(nullptr, bytes, in, out, (int32_t)0, (size_t)n,
-                                  rocprim::plus<int32_t>(), s));
-  void* t = tmp.ensure(bytes);
-  PGX_HIP(rocprim::exclusive_scan(t, bytes, in, out, (int32_t)0, (size_t)n, rocprim::plus<int32_t>(), s));
-}
-
 void exscan_u8_i32(const uint8_t* in, int32_t* out, int64_t n, hipStream_t s, DBuf& tmp) {
   if (n <= 0) return;
   auto it = rocprim::make_transform_iterator(in, U8ToInt());

@@ -232,7 +232,8 @@ template <typename T, int N> struct Engine : EngineBase {
   // dual form, fused inverse x + gather: base lines per y tile and z segments
   // per launch.  Small tiles (two z rows of 4 lines, 35 KB of LDS at 512^3)
   // let several blocks share a compute unit; measured at 512^3: 3.6 ms per
-  // launch against 3.7 ms for 7 and 4.3 ms for 15 base lines per tile.  The
+  // launch against 3.7 ms for 7 and 4.3 ms for 15 base lines per tile (3.3 since
+  // the points are loaded a row ahead).  The
   // TSC sweep keeps three z rows of YTT + 2 lines and its stage twiddles in
   // registers: 52 KB with 2 base lines per tile, three blocks per compute unit
   // (5.6 ms per launch at 512^3, against 7.7 ms with the LDS twiddle table and
@@ -1413,9 +1414,16 @@ template <typename T, int N> struct Engine : EngineBase {
     });
     const float* wl = w_given ? w_last.as<float>() : nullptr;
     if (n_pairs > 0) {
-      k_pair_grad<<<grid_for(n_pairs), 256, 0, s>>>(p_key.as<int32_t>(), p_i.as<int32_t>(),
-                                                    p_j.as<int32_t>(), gb, gcomp, std::max<int64_t>(n_pairs, 1),
-                                                    n_pairs, NN, gws_d, wl, gd);
+      const bool tab = n_pairs >= kPairTableFrom && n_pairs / kPairsPerGalaxy >= n_gal;
+      const int blocks = (int)((n_pairs + 256 * kPairGradRounds - 1) / (256 * kPairGradRounds));
+      auto run = [&](auto kernel, int grid, size_t lds) {
+        kernel<<<grid, 256, lds, s>>>(p_key.as<int32_t>(), p_i.as<int32_t>(), p_j.as<int32_t>(), gb, gcomp,
+                                      std::max<int64_t>(n_pairs, 1), n_pairs, 2 * __builtin_ctz((unsigned)N), gws_d, wl, gd);
+      };
+      if (tab)
+        run(k_pair_grad<true>, blocks, sizeof(GalaxyTable));
+      else
+        run(k_pair_grad<false>, grid_for(n_pairs), 0);
       launch_check("pair_grad");
     }
     if (n_gal > 0) {

@@ -1029,7 +1029,8 @@ template <typename T, int N> struct Engine : EngineBase {
 
   // starts[k] = first index of sorted keys with key >= k div, for k in [0, nkeys]
   void starts_of(const int32_t* sorted, int64_t n, int32_t div, int64_t nkeys, int32_t* starts, hipStream_t s) {
-    k_starts<<<grid_for(nkeys + 1), 256, 0, s>>>(sorted, n, div, nkeys, starts);
+    const int run = starts_run(n, nkeys);
+    k_starts<<<grid_for(nkeys / run + 1), 256, 0, s>>>(sorted, n, div, nkeys, run, starts);
     launch_check("starts");
   }
 

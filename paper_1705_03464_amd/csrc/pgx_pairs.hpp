@@ -132,10 +132,12 @@ __device__ __forceinline__ int64_t lower_bound_key(const int32_t* __restrict__ k
 // A search per group of `run` entries, then steps of doubling length from each
 // entry to the next: one launch takes the place of a fill, a histogram and a
 // two-launch scan, however the keys are spread.  Sparse keys: run = 8 (4.4e5 keys
-// over 1.0e7 entries 29 us per launch, against 42 with run = 1); where entries
-// have many keys the steps are long and run = 1 (3.6e8 keys over 5.2e6 entries
-// 65 us, against 111 with run = 8).
-__host__ __device__ constexpr int starts_run(int64_t n, int64_t nkeys) { return n > 4 * nkeys ? 1 : 8; }
+// over 1.0e7 entries 29 us per launch, against 42 with run = 1).  run = 1 where
+// entries have many keys and the steps are long (3.6e8 keys over 5.2e6 entries
+// 65 us, against 111), and up to 2^20 entries, fewer than fill the chip's
+// wavefronts twice, where the chain of searches is the time (pair build +
+// forward at 64^3 389 us, against 414).
+__host__ __device__ constexpr int starts_run(int64_t n, int64_t nkeys) { return nkeys <= (1 << 20) || n > 4 * nkeys ? 1 : 8; }
 static __global__ void k_starts(const int32_t* __restrict__ key, int64_t n, int32_t div, int64_t nkeys, int run,
                                 int32_t* __restrict__ starts) {
   const int64_t k0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * run;

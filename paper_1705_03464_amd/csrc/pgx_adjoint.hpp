@@ -480,7 +480,7 @@ k_xgather(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> p
     const int f = t == 0 ? slot_fa[slot] : slot_fb[slot];
     scs[l * 2 + t] = scale * (fscale && f >= 0 ? (T)fscale[f] : (T)1);
   }
-  const int total = br.build([&](int r, int& s, int& e) {
+  const int64_t total = br.build([&](int r, int& s, int& e) {
     task_source<T, N, W, TSC>(tasks, n_tasks, rev, 0, r, slot_fa, slot_fb, ps.line_start, s, e);
   });
   line_fft<Sh, 1>(v, t, line, tw_s, wave_sync);
@@ -490,7 +490,7 @@ k_xgather(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> p
   block_sync();
   typename PointRanges<NR, NT>::Walk walk;
 #pragma unroll 2
-  for (int i = tid; i < total; i += NT) {
+  for (int64_t i = tid; i < total; i += NT) {
     const int p = walk.point(br, i);
     const int q = walk.r % NB, lp = walk.r / NB;  // lp = 2 l + part
     const T fy = ps.fy[p], fz = ps.fz[p], fx = ps.fx[p];

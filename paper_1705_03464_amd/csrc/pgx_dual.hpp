@@ -605,7 +605,7 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
   C<T>* line = lines + l * LL;
 #pragma unroll
   for (int m = 0; m < E; ++m) line[lpad(t + TPL * m)] = C<T>{0, 0};
-  const int total = br.build([&](int r, int& s, int& e) {
+  const int64_t total = br.build([&](int r, int& s, int& e) {
     const int q = r % NB, y = y_base + l0 + r / NB;
     const int by = (TSC ? y + q % 3 - 1 : y - (q & 1)) & (N - 1);
     const int bz = (TSC ? z + q / 3 - 1 : z - (q >> 1)) & (N - 1);
@@ -620,7 +620,8 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
     int f, p;
     bool on;
   };
-  auto fetch = [&](const PointRanges<NR, 64>& pr, int count, typename PointRanges<NR, 64>::Walk& walk, int i) {
+  auto fetch = [&](const PointRanges<NR, 64>& pr, int64_t count, typename PointRanges<NR, 64>::Walk& walk,
+                   int64_t i) {
     Point a;
     a.on = i < count;
     a.key = NR * N + lane;  // idle lanes: past every real key, each its own
@@ -697,9 +698,9 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
   // points first, first + step, .. of the ranges `pr` into this wavefront's lines
   auto scatter = [&](const PointRanges<NR, 64>& pr, typename PointRanges<NR, 64>::Walk wk, int first, int step,
                      const float2* cq, int slot) {
-    const int count = pr.count;
+    const int64_t count = pr.count;
     Point a = fetch(pr, count, wk, first + lane);
-    for (int base = first; base < count; base += step) {
+    for (int64_t base = first; base < count; base += step) {
       const float2 c = a.on ? cq[a.f] : float2{0.f, 0.f};
       const Point nx = fetch(pr, count, wk, base + step + lane);
       WaveRuns r;

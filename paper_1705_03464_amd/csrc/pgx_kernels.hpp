@@ -65,109 +65,11 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The points of several ranges of a catalogue as one index range that NT
-// threads walk together: one wavefront (NT = 64) or the whole block.  The
-// x-direction passes give a line TPL threads, few on small grids, while a
-// clustered catalogue puts most of a block's points on one or two lines.  The
-// gathers share the points of a block's lines among all its threads; the
-// scatters share those of a wavefront's lines within it, so that a line's LDS
-// additions come from one wavefront and keep their order from run to run.
-// build(range): range(r, s, e) gives the bounds of range r < NR; returns the
-// number of points.  A Walk follows ascending combined indices, searching only
-// when it leaves a range.
-template <int NR, int NT> struct PointRanges {
-  int off[NR];    // combined index of the range's first point
-  int first[NR];  // its first point minus that
-  int part[NT / 64];
-  int count;      // all points
-  __device__ __forceinline__ static void sync() {
-    if constexpr (NT == 64) wave_sync();
-    else block_sync();
-  }
-  template <typename Fn> __device__ __forceinline__ int build(Fn&& range) {
-    constexpr int PER = (NR + NT - 1) / NT;
-    const int tid = threadIdx.x % NT, lane = tid & 63;
-    int s[PER], c[PER], sum = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      s[k] = c[k] = 0;
-      const int r = tid * PER + k;
-      if (r < NR) {
-        int e = 0;
-        range(r, s[k], e);
-        c[k] = e - s[k];
-      }
-      sum += c[k];
-    }
-    int inc = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int u = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += u;
-    }
-    int base = inc - sum, total = __shfl(inc, 63, 64);
-    if constexpr (NT > 64) {
-      if (lane == 63) part[tid >> 6] = inc;
-      block_sync();
-      total = 0;
-#pragma unroll
-      for (int w = 0; w < NT / 64; ++w) {
-        const int v = part[w];
-        if (w < tid >> 6) base += v;
-        total += v;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int r = tid * PER + k;
-      if (r < NR) {
-        off[r] = base;
-        first[r] = s[k] - base;
-      }
-      base += c[k];
-    }
-    if (tid == 0) count = total;
-    sync();
-    return total;
-  }
-  __device__ __forceinline__ int find(int i) const {
-    int r = 0;
-    constexpr int TOP = NR <= 1 ? 0 : 1 << (31 - __builtin_clz(NR - 1));
-#pragma unroll
-    for (int step = TOP; step > 0; step >>= 1)
-      if (((NR & (NR - 1)) == 0 || r + step < NR) && off[r + step] <= i) r += step;
-    return r;
-  }
-  struct Walk {
-    int r = 0, next = 0, shift = 0;
-    // point of combined index i (ascending from call to call); its range is r
-    __device__ __forceinline__ int point(const PointRanges& b, int i) {
-      if (i >= next) {
-        r = b.find(i);
-        next = r + 1 < NR ? b.off[r + 1] : 0x7FFFFFFF;
-        shift = b.first[r];
-      }
-      return i + shift;
-    }
-  };
-};
+}  // namespace pgx
 
-// Whether the NW wavefronts of a scatter block take the wavefronts' points one
-// after another together, each into its own copy of the lines, instead of each
-// its own: trips of 64 NW points plus the copies' sum and two barriers per
-// wavefront (about three trips), against the trips of the most crowded one.
-// Depends on the points only, so every run adds in the same order.
-template <int NR, int NW>
-__device__ __forceinline__ bool scatter_together(const PointRanges<NR, 64>* wave_ranges) {
-  int most = 0, trips = 0;
-#pragma unroll
-  for (int g = 0; g < NW; ++g) {
-    const int n = wave_ranges[g].count;
-    most = n > most ? n : most;
-    trips += n / (64 * NW) + 4;
-  }
-  return trips < most / 64;
-}
+#include "pgx_ranges.hpp"
+
+namespace pgx {
 
 template <typename T, typename Sh>
 __device__ __forceinline__ void load_twiddles(C<T>* tw_s, const C<T>* __restrict__ tw_g) {
@@ -413,7 +315,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
     const int f = t == 0 ? slot_fa[slot] : slot_fb[slot];
     scs[l * 2 + t] = fscale && f >= 0 ? (T)fscale[f] : (T)1;
   }
-  const int total = br.build([&](int r, int& s, int& e) {
+  const int64_t total = br.build([&](int r, int& s, int& e) {
     task_source<T, N, W, TSC>(tasks, n_tasks, rev, l0, r, slot_fa, slot_fb, ps.line_start, s, e);
   });
   struct Point {
@@ -421,7 +323,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
     int x0, r;
   };
   typename PointRanges<NR, 64>::Walk walk;
-  auto fetch = [&](int i) {
+  auto fetch = [&](int64_t i) {
     Point a{(T)0, (T)0, (T)0, (T)0, (T)0, 0, -1};
     if (i < total) {
       const int p = walk.point(br, i);
@@ -438,7 +340,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
   // twiddles; no barrier follows, so no wavefront waits for a crowded one
   block_sync();
   Point a = fetch(lane);
-  for (int base = 0; base < total; base += 64) {
+  for (int64_t base = 0; base < total; base += 64) {
     const Point nx = fetch(base + 64 + lane);
     const bool ok = a.r >= 0;
     const int r = ok ? a.r : 0, q = r % NB, lp = 2 * l0 + r / NB;  // lp = 2 line + part

@@ -137,6 +137,21 @@ struct HostBlock {
   void alloc(size_t n) { PGX_HIP(hipHostMalloc(&p, n, hipHostMallocDefault)); }
 };
 
+// Event made on first use.
+struct Event {
+  hipEvent_t e = nullptr;
+  Event() = default;
+  Event(const Event&) = delete;
+  Event& operator=(const Event&) = delete;
+  ~Event() {
+    if (e) (void)hipEventDestroy(e);
+  }
+  hipEvent_t get() {
+    if (!e) PGX_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    return e;
+  }
+};
+
 struct EngineBase {
   virtual ~EngineBase() {
     gf.reset();
@@ -255,6 +270,7 @@ template <typename T, int N> struct Engine : EngineBase {
 
   // three error flags, pair count, pairs per field, first task of each batch
   HostBlock host;
+  Event ingested;  // the catalogue's flags are written
   int* h_err() { return static_cast<int*>(host.p); }
   int64_t* h_count() { return static_cast<int64_t*>(host.p) + 2; }
   int64_t* h_fields() { return static_cast<int64_t*>(host.p) + 3; }
@@ -494,6 +510,46 @@ template <typename T, int N> struct Engine : EngineBase {
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, 1 << 16));
   }
 
+  // what k_ingest found (its stream has been waited for)
+  void refuse_flagged() {
+    const int* err = h_err();
+    PGX_REQUIRE(!err[0], PGX_EINVAL, "non-finite galaxy position");
+    PGX_REQUIRE(!err[1], PGX_EINVAL, "galaxy position outside [0, L)");
+    PGX_REQUIRE(!err[2], PGX_EINVAL, "weights must be finite and >= 0");
+  }
+
+  // Validates the catalogue (flags, and the event `ingested`, for the caller),
+  // keeps its positions for the multipoles and makes the cell list: cells of the
+  // galaxies in cell order (s_k1), their catalogue indices (s_v1) and positions
+  // (s_px, s_py, s_pz), the cells' starts (s_cs).
+  void cell_list(const double* x, const double* y, const double* z, const float* w, int64_t n, double side, int nc,
+                 hipStream_t s) {
+    const int64_t ncell = (int64_t)nc * nc * nc;
+    int* err = h_err();
+    err[0] = err[1] = err[2] = 0;
+    int32_t* ck = s_k0.get<int32_t>(n);
+    int32_t* ci = s_v0.get<int32_t>(n);
+    int32_t* cks = s_k1.get<int32_t>(n);
+    int32_t* perm = s_v1.get<int32_t>(n);
+    if (n > 0) {
+      double* kx = pos_x.get<double>(n);
+      double* ky = pos_y.get<double>(n);
+      double* kz = pos_z.get<double>(n);
+      k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, ck, ci, kx, ky, kz, err);
+      launch_check("ingest");
+      PGX_HIP(hipEventRecord(ingested.get(), s));
+    }
+    sort_pairs_i32(ck, cks, ci, perm, n, bits_for(ncell), s, s_tmp);
+    starts_of(cks, n, 1, ncell, s_cs.get<int32_t>(ncell + 1), s);
+    double* px = s_px.get<double>(n);
+    double* py = s_py.get<double>(n);
+    double* pz = s_pz.get<double>(n);
+    if (n > 0) {
+      k_gather_pos<<<grid_for(n), 256, 0, s>>>(perm, x, y, z, n, px, py, pz);
+      launch_check("gather_pos");
+    }
+  }
+
   void pairs_build(const double* x, const double* y, const double* z, const float* w, int64_t n,
                    hipStream_t s, int64_t* n_pairs_out, int64_t* counts, double* wsum) override {
     PGX_REQUIRE(n >= 0 && n < INT32_MAX, PGX_EINVAL, "n_gal must be in [0, 2^31)");
@@ -507,28 +563,31 @@ template <typename T, int N> struct Engine : EngineBase {
     int nc = (int)std::floor(cfg.L / (cfg.smax * (1.0 + 1e-12)));
     PGX_REQUIRE(nc >= 3, PGX_EINVAL, "maximum pair separation must be < L/3");
     const double side = cfg.L / nc;
-    const int64_t ncell = (int64_t)nc * nc * nc;
-    int32_t* ck = s_k0.get<int32_t>(n);
-    int32_t* ci = s_v0.get<int32_t>(n);
-    int32_t* cks = s_k1.get<int32_t>(n);
-    int32_t* perm = s_v1.get<int32_t>(n);
-    int* err = h_err();
-    err[0] = err[1] = err[2] = 0;
-    if (n > 0) {
-      k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, ck, ci, pos_x.get<double>(n),
-                                           pos_y.get<double>(n), pos_z.get<double>(n), err);
-      launch_check("ingest");
+    try {
+      cell_list(x, y, z, w, n, side, nc, s);
+    } catch (const Error&) {
+      // a buffer that does not fit: a wrong catalogue is refused as such first
+      // (and nothing in flight writes the flags when the next build clears them)
+      if (n > 0) {
+        k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, nullptr, nullptr, nullptr, nullptr,
+                                             nullptr, h_err());
+        if (hipStreamSynchronize(s) == hipSuccess) refuse_flagged();
+        (void)hipGetLastError();
+      }
+      throw;
     }
-    sort_pairs_i32(ck, cks, ci, perm, n, bits_for(ncell), s, s_tmp);
-    int32_t* cstart = s_cs.get<int32_t>(ncell + 1);
-    starts_of(cks, n, 1, ncell, cstart, s);
-    double* px = s_px.get<double>(n);
-    double* py = s_py.get<double>(n);
-    double* pz = s_pz.get<double>(n);
     if (n > 0) {
-      k_gather_pos<<<grid_for(n), 256, 0, s>>>(perm, x, y, z, n, px, py, pz);
-      launch_check("gather_pos");
+      // the flags, read while the cell list is being made: 2 us of a small pass's
+      // 387, and a wrong catalogue is refused before its pairs are counted
+      PGX_HIP(hipEventSynchronize(ingested.e));
+      refuse_flagged();
     }
+    const int32_t* cks = s_k1.as<int32_t>();
+    const int32_t* perm = s_v1.as<int32_t>();
+    const int32_t* cstart = s_cs.as<int32_t>();
+    const double* px = s_px.as<double>();
+    const double* py = s_py.as<double>();
+    const double* pz = s_pz.as<double>();
     PairCfg pc;
     pc.L = cfg.L;
     pc.halfL = cfg.L * 0.5;
@@ -555,11 +614,6 @@ template <typename T, int N> struct Engine : EngineBase {
       k_publish<<<1, 1, 0, s>>>(off + n, h_count());
       launch_check("publish");
       PGX_HIP(hipStreamSynchronize(s));
-      // the catalogue's flags, read with the count (a rejected catalogue has been
-      // counted for nothing)
-      PGX_REQUIRE(!err[0], PGX_EINVAL, "non-finite galaxy position");
-      PGX_REQUIRE(!err[1], PGX_EINVAL, "galaxy position outside [0, L)");
-      PGX_REQUIRE(!err[2], PGX_EINVAL, "weights must be finite and >= 0");
       P = *h_count();
     }
     PGX_REQUIRE(P < (int64_t)INT32_MAX, PGX_ENOTSUP, "pair count reaches 2^31");

@@ -73,9 +73,9 @@ __device__ __forceinline__ void cic_of(double x, double gscale, int N, int& i0, 
 // Validation of a catalogue (err, three words of host memory that the host has
 // cleared: non-finite position, position outside [0, L), bad weight; plain
 // stores, as the lanes that write one all write 1), the cell of each galaxy and
-// the positions kept for the multipoles, one pass.  Rejected positions are dealt
-// out over the cells, so that the pair count that still runs over them is no
-// longer than a uniform catalogue's.
+// the positions kept for the multipoles, one pass.  Rejected positions go to
+// cell 0: the cell list is made of them, but the host has read the flags before
+// anything walks it.  Without the outputs (key null) it validates only.
 __device__ __forceinline__ void raise_flag(int* f) {
   __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -94,11 +94,11 @@ static __global__ void k_ingest(const double* __restrict__ x, const double* __re
     const float v = w[i];
     if (!isfinite(v) || v < 0.0f) raise_flag(err + 2);
   }
-  const int ncell = nc * nc * nc;
+  if (!key) return;
   const int cx = ok ? min((int)(a / side), nc - 1) : 0;
   const int cy = ok ? min((int)(b / side), nc - 1) : 0;
   const int cz = ok ? min((int)(c / side), nc - 1) : 0;
-  key[i] = ok ? (cx * nc + cy) * nc + cz : (int)(i % ncell);
+  key[i] = (cx * nc + cy) * nc + cz;
   idx[i] = (int32_t)i;
   kx[i] = a;
   ky[i] = b;

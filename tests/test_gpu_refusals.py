@@ -1,0 +1,53 @@
+"""A wrong catalogue is refused as such (PGX_EINVAL) whatever the workspace: in
+regions from below the plan's tables up to the whole build, a bad position or
+weight is never reported as a lack of room once the tables fit, and the flags
+of a refused or failed build do not reach the next one."""
+import numpy as np
+import pytest
+
+from synth import get_config
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _dev(a, dt=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=dt, device="cuda")
+
+
+def _code(plan, x, y, z, w=None):
+    """Status of one build (0: built)."""
+    from paper_1705_03464_amd import PgxError
+    try:
+        plan.pairs_build(x, y, z, w=w)
+    except PgxError as e:
+        return e.code
+    return 0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_wrong_catalogues_are_refused_before_room_is_short(precision):
+    from paper_1705_03464_amd import Plan
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = get_config("cfg4tiny")
+    cat = wl.catalog()
+    x, y, z = _dev(cat.x), _dev(cat.y), _dev(cat.z)
+    far, nan, neg = x.clone(), x.clone(), torch.ones(cat.n, dtype=torch.float32, device="cuda")
+    far[cat.n // 2], nan[-1], neg[0] = wl.L, float("nan"), -1.0
+    seen = {0: 0, 2: 0}
+    size = 32 << 10
+    while size < 64 << 20:
+        plan = Plan.from_workload(wl, precision=precision)
+        plan.set_workspace(size)
+        codes = [_code(plan, far, y, z), _code(plan, nan, y, z), _code(plan, x, y, z, w=neg)]
+        good = _code(plan, x, y, z)
+        tables = plan.workspace_used()[0] > 0
+        print(f"{precision} workspace {size >> 10} KiB: tables {'fit' if tables else 'do not fit'}, "
+              f"refusals {codes}, good catalogue {good}", flush=True)
+        assert good in (0, 2)
+        assert codes == ([1, 1, 1] if tables else [2, 2, 2])
+        seen[good] += tables
+        plan.close()
+        size = size * 5 // 4
+    assert seen[0] >= 2 and seen[2] >= 4  # both sides of the build's needs were tried

@@ -29,7 +29,11 @@
  *     its own (grown on demand, released by pgx_plan_destroy); with a
  *     workspace attached (pgx_set_workspace) every device buffer of the plan
  *     is placed in that caller-owned region instead and the plan calls
- *     neither hipMalloc nor hipFree.
+ *     neither hipMalloc nor hipFree.  Either way the plan's first device work
+ *     also takes one block of page-locked host memory (hipHostMalloc; about
+ *     32 + 10 n_fields bytes) for the flags and counts that it reads back; it
+ *     is released with the plan's device state (pgx_plan_destroy,
+ *     pgx_set_workspace).
  *   - `stream` is a hipStream_t (NULL = the null stream).  Calls enqueue work
  *     on it; calls that return host values synchronise it (stated below).
  *   - Every call returns a pgx_status; no exception or abort crosses the ABI.
@@ -37,8 +41,9 @@
  *   - A plan is not thread-safe: use one plan per host thread and stream.
  *   - Fault injection, for tests of the error paths: while the environment
  *     variable PGX_DEBUG_FAIL_ALLOC holds n >= 1, the n-th allocation from the
- *     HIP allocator (counted from when the variable took that value) fails as
- *     an out-of-memory error would: calls needing that buffer return
+ *     HIP allocator, device or page-locked host memory (counted from when the
+ *     variable took that value), fails as an out-of-memory error would: calls
+ *     needing that buffer return
  *     PGX_EHIP, optional stores are skipped.  The plan stays usable.
  */
 #ifndef PGX_H

@@ -134,7 +134,12 @@ struct HostBlock {
   ~HostBlock() {
     if (p) (void)hipHostFree(p);
   }
-  void alloc(size_t n) { PGX_HIP(hipHostMalloc(&p, n, hipHostMallocDefault)); }
+  void alloc(size_t n) {
+    if (injected_alloc_failure())
+      throw Error(PGX_EHIP, "hipHostMalloc of " + std::to_string(n) +
+                                " bytes: injected failure (PGX_DEBUG_FAIL_ALLOC)");
+    PGX_HIP(hipHostMalloc(&p, n, hipHostMallocDefault));
+  }
 };
 
 // Event made on first use.

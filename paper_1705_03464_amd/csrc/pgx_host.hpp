@@ -149,9 +149,9 @@ inline size_t free_device_bytes() {
 inline size_t spare_device_bytes() { return (t_heap || t_session) ? 0 : ((size_t)4 << 30); }
 
 // Fault injection for tests of the error paths: while the environment
-// variable PGX_DEBUG_FAIL_ALLOC holds n >= 1, the n-th device allocation from
-// the HIP allocator (counted from the moment the variable took that value)
-// fails as if the device were out of memory: a required buffer raises
+// variable PGX_DEBUG_FAIL_ALLOC holds n >= 1, the n-th allocation from the HIP
+// allocator, device or page-locked host memory (counted from the moment the
+// variable took that value), fails as if there were no room: a required buffer raises
 // PGX_EHIP, an optional store is skipped.  Unset, it costs one getenv per
 // allocation.
 inline bool injected_alloc_failure() {

@@ -51,3 +51,28 @@ def test_wrong_catalogues_are_refused_before_room_is_short(precision):
         plan.close()
         size = size * 5 // 4
     assert seen[0] >= 2 and seen[2] >= 4  # both sides of the build's needs were tried
+
+
+@pytest.mark.parametrize("workspace", [False, True])
+def test_page_locked_host_memory_can_be_missing(workspace, monkeypatch):
+    """The plan's block of page-locked host memory is the first allocation of its
+    first device work; when it fails (injected) the call returns PGX_EHIP and the
+    plan works afterwards, with its own device memory and with a workspace, where
+    it is the only allocation."""
+    from paper_1705_03464_amd import PgxError, Plan
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = get_config("cfg4tiny")
+    cat = wl.catalog()
+    x, y, z = _dev(cat.x), _dev(cat.y), _dev(cat.z)
+    plan = Plan.from_workload(wl, precision="fp32")
+    if workspace:
+        plan.set_workspace(512 << 20)
+    monkeypatch.setenv("PGX_DEBUG_FAIL_ALLOC", "1")
+    with pytest.raises(PgxError) as e:
+        plan.pairs_build(x, y, z)
+    assert e.value.code == 3 and "hipHostMalloc" in str(e.value) and "injected" in str(e.value)
+    monkeypatch.delenv("PGX_DEBUG_FAIL_ALLOC")
+    P, _ = plan.pairs_build(x, y, z)
+    assert P > 0
+    plan.close()

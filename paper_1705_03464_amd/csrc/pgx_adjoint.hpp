@@ -164,7 +164,7 @@ k_kgen_x(const double* __restrict__ coef, int R, const int32_t* __restrict__ slo
          const int32_t* __restrict__ slot_fb, int pwx, int pwy, int pwz, BinMap bm,
          C<T>* __restrict__ out, int64_t out_slot, const C<T>* __restrict__ tw_g,
          const float* __restrict__ fscale = nullptr, int nh = 0) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
   load_twiddles<T, Sh>(tw_s, tw_g);
@@ -229,7 +229,7 @@ k_zback(C<T>* x, int64_t x_slot, const uint8_t* __restrict__ pflag,
         const int32_t* __restrict__ slot_fp, int n_slots, const C<T>* __restrict__ ky_in,
         int64_t ky_slot, int pwz, const C<T>* __restrict__ fg, C<T>* __restrict__ acc_out,
         const C<T>* __restrict__ tw_g, const C<T>* __restrict__ spec = nullptr) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   constexpr bool PIPE = E <= 8;  // register room for a second set of columns
   __shared__ C<T> tw_s[Sh::tw_entries()];
@@ -406,7 +406,7 @@ template <typename T, typename Sh, int W>
 static __global__ void __launch_bounds__(W * Sh::TPL)
 k_zinit(const C<T>* __restrict__ ky_in, int pwz, const C<T>* __restrict__ fg,
         C<T>* __restrict__ acc_out, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
@@ -455,7 +455,7 @@ k_xgather(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> p
           const int32_t* __restrict__ slot_fa, const int32_t* __restrict__ slot_fb,
           const C<T>* __restrict__ in, T scale, float* __restrict__ acc, int64_t qs,
           const C<T>* __restrict__ tw_g, const float* __restrict__ fscale = nullptr) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int NT = W * TPL, NB = line_sources<TSC>(), NR = W * 2 * NB;
   constexpr int64_t NN = (int64_t)N * N;
   __shared__ C<T> tw_s[Sh::tw_entries()];

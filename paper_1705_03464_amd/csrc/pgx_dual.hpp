@@ -49,7 +49,7 @@ static __global__ void __launch_bounds__(W * Sh::TPL)
 k_zconv(const C<T>* __restrict__ ky_in, int64_t ky_slot, int n_slots, int pwz,
         const C<T>* __restrict__ fg, C<T>* __restrict__ out, int64_t out_slot,
         const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   constexpr bool PIPE = E <= 8;
   __shared__ C<T> tw_s[tw_lds_entries<Sh, kZTwReg>()];
@@ -213,7 +213,7 @@ static __global__ void __launch_bounds__((YT + 1) * Sh::TPL)
 k_xinv_gather_sweep(PointSet<T> ps, const int32_t* __restrict__ perm, int64_t P,
                     const C<T>* __restrict__ U, int64_t u_slot, int zlen, int b0, int R,
                     float* __restrict__ gv, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), NG = YT + 1;
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>(), NG = YT + 1;
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> rows[2][NG][LL];
   load_twiddles<T, Sh>(tw_s, tw_g);
@@ -318,7 +318,7 @@ static __global__ void __launch_bounds__((YT + 2) * Sh::TPL)
 k_xinv_gather_sweep_tsc(PointSet<T> ps, const int32_t* __restrict__ perm, int64_t P,
                         const C<T>* __restrict__ U, int64_t u_slot, int zlen, int b0, int R,
                         float* __restrict__ gv, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), NG = YT + 2;
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>(), NG = YT + 2;
   // stage twiddles in registers: the LDS holds only the three rows of lines
   __shared__ C<T> rows[3][NG][LL];
   const int g = threadIdx.x / TPL, t = threadIdx.x % TPL;
@@ -587,7 +587,7 @@ k_xscatter_dual(PointSet<T> ps, const int32_t* __restrict__ lfield, const float2
                 int F, int q0, int nq, C<T>* __restrict__ out, int64_t out_slot,
                 const C<T>* __restrict__ tw_g, const float* __restrict__ yl = nullptr, int nh = 1,
                 int64_t P = 0) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int NT = W * TPL, NB = TSC ? 9 : 4, NX = TSC ? 3 : 2, KEEP = 2;
   // 512^3 and larger: enough blocks to hide a crowded line (3.36 ms per launch
   // without the second mode, 3.52 with it; 256^3: 0.66 and 0.59)
@@ -767,7 +767,7 @@ static __global__ void __launch_bounds__(W * Sh::TPL)
 k_zdual_acc(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
             const C<T>* __restrict__ ky_in, int64_t ky_slot, int pwz, C<T>* __restrict__ acc_out,
             const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   constexpr bool PIPE = E <= 8;
   __shared__ C<T> tw_s[tw_lds_entries<Sh, kZTwReg>()];
@@ -901,7 +901,7 @@ template <typename T, typename Sh, int W>
 static __global__ void __launch_bounds__(W * Sh::TPL)
 k_kspec(const C<T>* __restrict__ ky_in, int64_t ky_slot, int pwz, C<T>* __restrict__ ks,
         int64_t ks_slot, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), H = N / 2;
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>(), H = N / 2;
   constexpr int64_t NN = (int64_t)N * N;
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
@@ -949,7 +949,7 @@ template <typename T, typename Sh, int W>
 static __global__ void __launch_bounds__(W * Sh::TPL, Sh::E <= 8 ? 8 : 1)
 k_zconv_ks(const C<T>* __restrict__ ks, int64_t ks_slot, int n_slots, const C<T>* __restrict__ fg,
            C<T>* __restrict__ out, int64_t out_slot, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), H = N / 2;
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>(), H = N / 2;
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   __shared__ C<T> tw_s[tw_lds_entries<Sh, false>()];
   __shared__ C<T> lines[W][LL];
@@ -1032,7 +1032,7 @@ k_zdual_acc_ks(const C<T>* __restrict__ x, int64_t x_slot, int n_slots,
                const C<T>* __restrict__ ks, int64_t ks_slot, const float2* __restrict__ gc,
                const C<T>* __restrict__ fg, int first, C<T>* __restrict__ acc_out,
                const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>(), H = N / 2;
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>(), H = N / 2;
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   // Shapes of at most 8 elements per thread run lean: the galaxy-kernel sum
   // in registers, stage twiddles from the LDS table, the kernel values loaded

@@ -165,10 +165,11 @@ __device__ __forceinline__ int lpad(int i) { return i + (i >> kPadShift); }
 // unit of the largest value (0.5 to 1.3 of it, by the order of the additions
 // alone).  The passes of a 64^3 grid are bound by their launches, so this costs
 // a few per cent there; larger grids would pay with half their occupancy.
-template <typename T, int N> __host__ __device__ constexpr bool fft64() { return sizeof(T) == 4 && N == 64; }
-// LDS entries of one line (of type C<T>; 64-point lines have room for C<double>)
-template <int N> constexpr int lds_line_elems() {
-  return (N == 64 ? 2 : 1) * (N + (N >> kPadShift) + kLineExtra);
+template <typename T, int N> __host__ __device__ constexpr bool fft64() { return sizeof(T) == 4 && N <= 64; }
+// LDS entries (of type C<T>) of one line: those transformed in FP64 have room for
+// C<double>
+template <int N, typename T = float> constexpr int lds_line_elems() {
+  return (fft64<T, N>() ? 2 : 1) * (N + (N >> kPadShift) + kLineExtra);
 }
 
 // Twiddle providers for stage s >= 1 of butterfly q (j = t + TPL*q), radix
@@ -286,7 +287,7 @@ template <typename Sh> constexpr bool pad_linear() {
 
 // Full line transform.  On entry v[m] holds element t + TPL*m of the line; on
 // exit v[m] holds output element t + TPL*m.  `line` is this line's LDS buffer
-// (lds_line_elems<N>() entries); `tw` the per-stage forward twiddle tables in LDS.
+// (lds_line_elems<N, T>() entries); `tw` the per-stage forward twiddle tables in LDS.
 // SYNC is a callable that synchronises all threads sharing `line`.
 template <typename Sh, int DIR, typename T, typename Sync, typename TW>
 __device__ __forceinline__ void line_fft_tw(C<T>* v, int t, C<T>* line, const TW& tw, Sync sync) {

@@ -288,7 +288,7 @@ k_xscatter(const int32_t* __restrict__ tasks, int n_tasks, int rev, PointSet<T> 
            const int32_t* __restrict__ slot_fa, const int32_t* __restrict__ slot_fb,
            C<T>* __restrict__ out, const C<T>* __restrict__ tw_g,
            const float* __restrict__ fscale = nullptr) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int NT = W * TPL, NB = line_sources<TSC>(), NX = TSC ? 3 : 2;
   constexpr int LW = 64 / TPL, NR = LW * 2 * NB;  // lines and sources of a wavefront
   // additions to a node: at 64^3 in FP64 (the lines hold FP64 there)
@@ -425,7 +425,7 @@ k_strided(const C<T>* in, C<T>* out, int64_t in_slot, int64_t out_slot,
           int64_t in_A, int64_t out_A, int64_t in_es, int64_t out_es, int pw,
           const uint8_t* __restrict__ lflag, const uint8_t* __restrict__ pflag,
           int64_t flag_slot, const int32_t* __restrict__ slot_fp, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   __shared__ C<T> tw_s[tw_lds_entries<Sh, false>()];
   __shared__ C<T> lines[W][LL];
   int xt = blockIdx.x, a = blockIdx.y, slot = blockIdx.z;
@@ -561,7 +561,7 @@ k_zcross(const C<T>* in, int64_t in_slot, const uint8_t* __restrict__ pflag,
          const int32_t* __restrict__ slot_fp, int n_slots, const C<T>* __restrict__ fg,
          C<T>* __restrict__ fg_out, C<T>* __restrict__ out, int64_t out_slot, int pw,
          const C<T>* __restrict__ tw_g, C<T>* __restrict__ spec = nullptr) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   constexpr int64_t NN = (int64_t)N * N, ZS = plane_stride<T, N>();
   // slot pipeline when a thread has room for a second set of columns
   constexpr bool PIPE = !GAL && E <= 8;
@@ -804,7 +804,7 @@ template <typename T, typename Sh, int W, int RMAX>
 static __global__ void __launch_bounds__(W * Sh::TPL)
 k_xinv_bins(const C<T>* __restrict__ in, int64_t in_slot, int pwx, int pwy, int pwz, BinMap bm,
             int R, double* __restrict__ part, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
   __shared__ double acc[2 * RMAX];
@@ -849,7 +849,7 @@ k_xinv_bins(const C<T>* __restrict__ in, int64_t in_slot, int pwx, int pwy, int 
 template <typename T, typename Sh, int W, int DIR>
 static __global__ void __launch_bounds__(W * Sh::TPL)
 k_xdense(C<T>* data, const C<T>* __restrict__ tw_g) {
-  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N>();
+  constexpr int N = Sh::n, E = Sh::E, TPL = Sh::TPL, LL = lds_line_elems<N, T>();
   __shared__ C<T> tw_s[Sh::tw_entries()];
   __shared__ C<T> lines[W][LL];
   load_twiddles<T, Sh>(tw_s, tw_g);

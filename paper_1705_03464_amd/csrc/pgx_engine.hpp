@@ -375,7 +375,7 @@ template <typename T, int N> struct Engine : EngineBase {
     const double F = c.F, R = c.R, Q = (c.R + 1) / 2, nfp = c.n_fp;
     const double nz = win_len(c.pw[2]), ny = win_len(c.pw[1]), nx = win_len(c.pw[0]);
     const double nd = (double)std::max<int64_t>(n, 1), pd = (double)std::max<int64_t>(P, 1);
-    int nc = (int)std::floor(c.L / (c.smax * (1.0 + 1e-12)));
+    const int nc = cells_per_side(c.L, c.smax);
     const double ncell = std::max(27.0, (double)nc * nc * nc);
     double b = 0.0;
     // galaxies: positions kept for the multipoles, cell-list scratch, point
@@ -565,7 +565,7 @@ template <typename T, int N> struct Engine : EngineBase {
     n_gal = n;
     const int F = cfg.F;
     // cell list: side >= maximum pair separation
-    int nc = (int)std::floor(cfg.L / (cfg.smax * (1.0 + 1e-12)));
+    const int nc = cells_per_side(cfg.L, cfg.smax);
     PGX_REQUIRE(nc >= 3, PGX_EINVAL, "maximum pair separation must be < L/3");
     const double side = cfg.L / nc;
     try {

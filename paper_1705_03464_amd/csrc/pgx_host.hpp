@@ -260,6 +260,16 @@ inline int grid_for(int64_t n, int threads = 256) {
 }
 
 // ----------------------------------------------------------------------------
+// Cells per side of the pair search's cell list: as many as leave each cell at
+// least the largest pair separation wide (a galaxy's partners are in the 27
+// cells around it), up to 1290, the most whose cube fits the 32-bit cell index.
+// ----------------------------------------------------------------------------
+constexpr int kMaxCellsPerSide = 1290;
+inline int cells_per_side(double L, double smax) {
+  return (int)std::min(std::floor(L / (smax * (1.0 + 1e-12))), (double)kMaxCellsPerSide);
+}
+
+// ----------------------------------------------------------------------------
 // Output-bin tables (host).  q = e / Delta, threshold t = q*q (FP64);
 // an integer square sum m is in bin k iff t_k <= m < t_{k+1}.
 // ----------------------------------------------------------------------------

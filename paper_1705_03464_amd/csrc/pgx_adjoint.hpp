@@ -558,16 +558,19 @@ struct GalaxyTable {
 // (field, line) the pairs keep the order of the pair search, which emits each
 // galaxy's pairs together, so runs of one galaxy in adjacent lanes are
 // summed across the wavefront first and only the last lane of each run adds
-// on.  What bounds the launch is the FP64 atomics to memory.  TABLE, for
-// crowded catalogues: a block takes kPairGradRounds x 256 consecutive pairs and
-// sums them per galaxy in LDS first, as the pairs of neighbouring lines are of
-// the same few galaxies; run sums before it only cost time (5.1 ms against 4.2).
-// At 3.6e8 pairs of 1e6 galaxies 9.0 -> 4.0 ms (12 KB of table and 8 rounds;
-// 4.3 with 6 KB and 4 rounds or 16 rounds, 8.7 with 48 KB: too few blocks per
-// unit).  With 7 pairs per galaxy (3.4e6 pairs) the table takes 0.30 ms against
-// 0.26: it is used from 64 pairs per galaxy on, and from as many pairs as give
-// each compute unit two blocks.
-constexpr int64_t kPairsPerGalaxy = 64, kPairTableFrom = 1 << 20;
+// on.  TABLE, for crowded catalogues, leaves fewer FP64 atomics to memory: a
+// block takes kPairGradRounds x 256 consecutive pairs and sums them per galaxy
+// in LDS first, as the pairs of neighbouring lines are of the same few galaxies;
+// run sums before it only cost time (5.1 ms against 4.2).  At 3.6e8 pairs of 2e6
+// galaxies 9.0 -> 4.0 ms (12 KB of table and 8 rounds; 4.3 with 6 KB and 4 rounds
+// or 16 rounds, 8.7 with 48 KB: too few blocks per unit).  It is used from 24
+// pairs per galaxy on, where clustered candidates cross over, without and with it
+// (us): 13 pairs per galaxy 138 and 157, 21 203 and 206, 25 1783 and 1363 (5.0e7
+// pairs), 31 264 and 202, 47 360 and 242, 180 1259 and 621; a dense uniform box
+// would gain earlier (9 pairs per galaxy 378 and 350, 27 1081 and 713, 109 4370
+// and 1964); and from as many pairs as give each compute unit two blocks (4.7e5
+// pairs of 2e4 galaxies 23 and 33).
+constexpr int64_t kPairsPerGalaxy = 24, kPairTableFrom = 1 << 20;
 constexpr int kPairGradRounds = 8;
 template <bool TABLE>
 static __global__ void __launch_bounds__(256)

@@ -1140,11 +1140,15 @@ template <typename T, int N> struct Engine : EngineBase {
   }
 
   // Grid of the Pi scatter: NN / WX blocks of lines, the slots split over
-  // blockIdx.y until the launch has about kDualScatterBlocks blocks.  A block
-  // with a crowded line outlasts the others by its points times its slots;
-  // splitting costs reading every point once per part.  256^3 (8192 blocks of
-  // lines, 10 slots): 0.64 ms whole, 0.54 in 2 parts, 0.56 in 5, 0.61 in 10
-  // (TSC 1.59, 1.23, 1.15, 1.22); 512^3 (65536 blocks): 3.22 whole, 3.39 in 2.
+  // blockIdx.y until the launch has about kDualScatterBlocks blocks (10 slots: one
+  // each at 64^3 and 128^3, 3 parts at 256^3, whole at 512^3).  A block with a
+  // crowded line outlasts the others by its points times its slots; splitting
+  // costs reading every point once per part.  us per launch of 10 slots whole, in
+  // 2, 3, 5 and 10 parts: 64^3 270, 138, 119, 75, 49 (2e4 HOD pairs) and 160, 84,
+  // 74, 48, 33 (8e3 pairs); 128^3 274, 165, 147, 115, 106 (5e4 pairs), with TSC
+  // 701, 410, 367, 276, 252; 256^3 (4e5 pairs) 678, 564, 569, 600, 703, with TSC
+  // 1648, 1324, 1285, 1285, 1444, and with 4.4e7 HOD pairs 37.6, 29.1, 27.9, 25.5,
+  // 25.1 ms; 512^3 (3.6e6 pairs) 3403, 3347, 3568, with TSC 7037, 6940, 7055.
   static constexpr int kDualScatterBlocks = 24576;
   static dim3 dual_scatter_grid(int nq) {
     const int nb = (int)(NN / WX);

@@ -219,11 +219,17 @@ template <bool TSC> constexpr int line_sources() { return TSC ? 16 : 4; }
 //  - grids below 256^3 (few blocks, everything in the caches): lines spread
 //    evenly over the task list, so that the neighbouring crowded lines of a
 //    cluster fall into different blocks (64^3, 9000 galaxies: 21 us per launch,
-//    28 in line order, 61 with the most crowded lines first);
+//    28 in line order, 61 with the most crowded lines first).  At 128^3, scatter
+//    and gather in us, spread and in line order: 4.4e6 HOD pairs 396 + 102 and 864
+//    + 219, with TSC 1198 + 343 and 2665 + 1221; 5e4 pairs 38 + 36 and 37 + 35,
+//    with TSC 77 + 93 and 80 + 77; 1.3e6 pairs of a uniform box 170 + 148 and 157 +
+//    112: little is lost where nothing is crowded;
 //  - larger grids: neighbouring lines, which read the same points, and runs of
 //    kTaskChunk blocks of them on one XCD, so the points come from its L2
 //    (1024^3, 16 fields: 18.7 ms per step, 21.3 with the most crowded first in
-//    the hardware's block order).
+//    the hardware's block order).  At 256^3, in line order and spread: 4e5 pairs
+//    345 + 291 and 358 + 313 us, 4.4e7 HOD pairs 1553 + 724 and 1524 + 714, 1.1e7
+//    pairs of a uniform box 1296 + 883 and 1363 + 1075.
 // rev: blocks in descending order (Engine::last_crowded; 3.7e8 HOD pairs at
 // 512^3: 7.9 ms per step, 8.5 ascending).
 constexpr int kTaskChunk = 32;

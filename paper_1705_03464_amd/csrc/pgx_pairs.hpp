@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pgx_starts.hpp"
+
 namespace pgx {
 
 struct PairCfg {
@@ -116,45 +118,11 @@ static __global__ void k_gather_pos(const int32_t* __restrict__ perm, const doub
   pz[p] = z[i];
 }
 
-// first index of the sorted keys with key >= t (binary search)
-__device__ __forceinline__ int64_t lower_bound_key(const int32_t* __restrict__ key, int64_t n, int64_t t) {
-  int64_t lo = 0, hi = n;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if ((int64_t)key[mid] < t)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-// starts[k] = first index of the sorted keys with key >= k div, for k in [0, nkeys].
-// A search per group of `run` entries, then steps of doubling length from each
-// entry to the next: one launch takes the place of a fill, a histogram and a
-// two-launch scan, however the keys are spread.  Sparse keys: run = 8 (4.4e5 keys
-// over 1.0e7 entries 29 us per launch, against 42 with run = 1).  run = 1 where
-// entries have many keys and the steps are long (3.6e8 keys over 5.2e6 entries
-// 65 us, against 111), and up to 2^20 entries, fewer than fill the chip's
-// wavefronts twice, where the chain of searches is the time (pair build +
-// forward at 64^3 389 us, against 414).
-__host__ __device__ constexpr int starts_run(int64_t n, int64_t nkeys) { return nkeys <= (1 << 20) || n > 4 * nkeys ? 1 : 8; }
+// starts[k] = first index of the sorted keys with key >= k div, for k in [0, nkeys]
+// (see range_starts)
 static __global__ void k_starts(const int32_t* __restrict__ key, int64_t n, int32_t div, int64_t nkeys, int run,
                                 int32_t* __restrict__ starts) {
-  const int64_t k0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * run;
-  if (k0 > nkeys) return;
-  int64_t lo = lower_bound_key(key, n, k0 * div);
-  for (int r = 0; r < run && k0 + r <= nkeys; ++r) {
-    const int64_t t = (k0 + r) * div;
-    // keys before lo are < t; step past those that still are
-    int64_t step = 1;
-    while (lo + step <= n && (int64_t)key[lo + step - 1] < t) {
-      lo += step;
-      step *= 2;
-    }
-    const int64_t m = step - 1 < n - lo ? step - 1 : n - lo;  // key[lo + step - 1] >= t, or past the end
-    lo += lower_bound_key(key + lo, m, t);
-    starts[k0 + r] = (int32_t)lo;
-  }
+  range_starts(key, n, div, nkeys, run, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, starts);
 }
 
 __device__ __forceinline__ int wrap_cell(int c, int nc) { return c < 0 ? c + nc : (c >= nc ? c - nc : c); }

@@ -142,21 +142,6 @@ struct HostBlock {
   }
 };
 
-// Event made on first use.
-struct Event {
-  hipEvent_t e = nullptr;
-  Event() = default;
-  Event(const Event&) = delete;
-  Event& operator=(const Event&) = delete;
-  ~Event() {
-    if (e) (void)hipEventDestroy(e);
-  }
-  hipEvent_t get() {
-    if (!e) PGX_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    return e;
-  }
-};
-
 struct EngineBase {
   virtual ~EngineBase() {
     gf.reset();
@@ -275,7 +260,10 @@ template <typename T, int N> struct Engine : EngineBase {
 
   // three error flags, pair count, pairs per field, first task of each batch
   HostBlock host;
-  Event ingested;  // the catalogue's flags are written
+  // number of the pair build, and device word that holds it when the build's
+  // catalogue is rejected
+  int32_t build_id = 0;
+  DBuf bad;
   int* h_err() { return static_cast<int*>(host.p); }
   int64_t* h_count() { return static_cast<int64_t*>(host.p) + 2; }
   int64_t* h_fields() { return static_cast<int64_t*>(host.p) + 3; }
@@ -416,6 +404,7 @@ template <typename T, int N> struct Engine : EngineBase {
     static_assert(N % W == 0 && N % WA == 0, "tile width must divide N");
     static_assert((N / W) * N % 8 == 0 && (N / WH) * N % 8 == 0, "z-pass grids are whole XCD rounds");
     host.alloc(24 + 8 * (size_t)std::max(cfg.F, 1) + 4 * ((size_t)cfg.n_fp + 2));
+    upload(bad, std::vector<int32_t>{0});
     upload(tw, twiddles<Sh>());
     upload(tw_alt, twiddles<ShA>());
     upload(lut1, cfg.bins.lut1.empty() ? std::vector<int16_t>{-1} : cfg.bins.lut1);
@@ -523,10 +512,10 @@ template <typename T, int N> struct Engine : EngineBase {
     PGX_REQUIRE(!err[2], PGX_EINVAL, "weights must be finite and >= 0");
   }
 
-  // Validates the catalogue (flags, and the event `ingested`, for the caller),
-  // keeps its positions for the multipoles and makes the cell list: cells of the
-  // galaxies in cell order (s_k1), their catalogue indices (s_v1) and positions
-  // (s_px, s_py, s_pz), the cells' starts (s_cs).
+  // Validates the catalogue (flags for the caller), keeps its positions for the
+  // multipoles and makes the cell list: cells of the galaxies in cell order (s_k1),
+  // their catalogue indices (s_v1) and positions (s_px, s_py, s_pz), the cells'
+  // starts (s_cs).
   void cell_list(const double* x, const double* y, const double* z, const float* w, int64_t n, double side, int nc,
                  hipStream_t s) {
     const int64_t ncell = (int64_t)nc * nc * nc;
@@ -540,9 +529,10 @@ template <typename T, int N> struct Engine : EngineBase {
       double* kx = pos_x.get<double>(n);
       double* ky = pos_y.get<double>(n);
       double* kz = pos_z.get<double>(n);
-      k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, ck, ci, kx, ky, kz, err);
+      build_id = build_id < INT32_MAX ? build_id + 1 : 1;
+      k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, ck, ci, kx, ky, kz, err,
+                                           bad.as<int32_t>(), build_id);
       launch_check("ingest");
-      PGX_HIP(hipEventRecord(ingested.get(), s));
     }
     sort_pairs_i32(ck, cks, ci, perm, n, bits_for(ncell), s, s_tmp);
     starts_of(cks, n, 1, ncell, s_cs.get<int32_t>(ncell + 1), s);
@@ -568,31 +558,6 @@ template <typename T, int N> struct Engine : EngineBase {
     const int nc = cells_per_side(cfg.L, cfg.smax);
     PGX_REQUIRE(nc >= 3, PGX_EINVAL, "maximum pair separation must be < L/3");
     const double side = cfg.L / nc;
-    try {
-      cell_list(x, y, z, w, n, side, nc, s);
-    } catch (const Error&) {
-      // a buffer that does not fit: a wrong catalogue is refused as such first
-      // (and nothing in flight writes the flags when the next build clears them)
-      if (n > 0) {
-        k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, nullptr, nullptr, nullptr, nullptr,
-                                             nullptr, h_err());
-        if (hipStreamSynchronize(s) == hipSuccess) refuse_flagged();
-        (void)hipGetLastError();
-      }
-      throw;
-    }
-    if (n > 0) {
-      // the flags, read while the cell list is being made: 2 us of a small pass's
-      // 387, and a wrong catalogue is refused before its pairs are counted
-      PGX_HIP(hipEventSynchronize(ingested.e));
-      refuse_flagged();
-    }
-    const int32_t* cks = s_k1.as<int32_t>();
-    const int32_t* perm = s_v1.as<int32_t>();
-    const int32_t* cstart = s_cs.as<int32_t>();
-    const double* px = s_px.as<double>();
-    const double* py = s_py.as<double>();
-    const double* pz = s_pz.as<double>();
     PairCfg pc;
     pc.L = cfg.L;
     pc.halfL = cfg.L * 0.5;
@@ -608,17 +573,34 @@ template <typename T, int N> struct Engine : EngineBase {
     pc.t1 = t1.as<double>();
     pc.t2 = t2.as<double>();
     pc.dmax2 = cfg.pair_dmax * cfg.pair_dmax;
-    int64_t* cnt = s_cnt.get<int64_t>(n + 1);
-    int64_t* off = s_off.get<int64_t>(n + 1);
     int64_t P = 0;
+    try {
+      cell_list(x, y, z, w, n, side, nc, s);
+      int64_t* cnt = s_cnt.get<int64_t>(n + 1);
+      int64_t* off = s_off.get<int64_t>(n + 1);
+      if (n > 0) {
+        k_pairs<false, T><<<pair_blocks(n), 64 * kPairWaves, 0, s>>>(
+            pc, s_px.as<double>(), s_py.as<double>(), s_pz.as<double>(), s_v1.as<int32_t>(), s_k1.as<int32_t>(),
+            s_cs.as<int32_t>(), n, cnt, nullptr, nullptr, nullptr, nullptr, bad.as<int32_t>(), build_id);
+        launch_check("pair_count");
+        exscan_i64(cnt, off, n + 1, s, s_tmp);
+        k_publish<<<1, 1, 0, s>>>(off + n, h_count());
+        launch_check("publish");
+      }
+    } catch (const Error&) {
+      // a buffer that does not fit: a wrong catalogue is refused as such first
+      // (and nothing in flight writes the flags when the next build clears them)
+      if (n > 0) {
+        k_ingest<<<grid_for(n), 256, 0, s>>>(x, y, z, w, n, cfg.L, side, nc, nullptr, nullptr, nullptr, nullptr,
+                                             nullptr, h_err(), nullptr, 0);
+        if (hipStreamSynchronize(s) == hipSuccess) refuse_flagged();
+        (void)hipGetLastError();
+      }
+      throw;
+    }
     if (n > 0) {
-      k_pairs<false, T><<<pair_blocks(n), 64 * kPairWaves, 0, s>>>(pc, px, py, pz, perm, cks, cstart, n, cnt,
-                                                                  nullptr, nullptr, nullptr, nullptr);
-      launch_check("pair_count");
-      exscan_i64(cnt, off, n + 1, s, s_tmp);
-      k_publish<<<1, 1, 0, s>>>(off + n, h_count());
-      launch_check("publish");
       PGX_HIP(hipStreamSynchronize(s));
+      refuse_flagged();  // (its pairs have not been counted)
       P = *h_count();
     }
     PGX_REQUIRE(P < (int64_t)INT32_MAX, PGX_ENOTSUP, "pair count reaches 2^31");
@@ -628,8 +610,9 @@ template <typename T, int N> struct Engine : EngineBase {
     int32_t* uj = s_j.get<int32_t>(P);
     int32_t* place = s_v0.get<int32_t>(P);
     if (P > 0) {
-      k_pairs<true, T><<<pair_blocks(n), 64 * kPairWaves, 0, s>>>(pc, px, py, pz, perm, cks, cstart, n, off, uk, ui,
-                                                                 uj, place);
+      k_pairs<true, T><<<pair_blocks(n), 64 * kPairWaves, 0, s>>>(
+          pc, s_px.as<double>(), s_py.as<double>(), s_pz.as<double>(), s_v1.as<int32_t>(), s_k1.as<int32_t>(),
+          s_cs.as<int32_t>(), n, s_off.as<int64_t>(), uk, ui, uj, place);
       launch_check("pair_emit");
     }
     // bucket by (field, line)

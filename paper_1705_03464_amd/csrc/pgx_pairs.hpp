@@ -75,9 +75,10 @@ __device__ __forceinline__ void cic_of(double x, double gscale, int N, int& i0, 
 // Validation of a catalogue (err, three words of host memory that the host has
 // cleared: non-finite position, position outside [0, L), bad weight; plain
 // stores, as the lanes that write one all write 1), the cell of each galaxy and
-// the positions kept for the multipoles, one pass.  Rejected positions go to
-// cell 0: the cell list is made of them, but the host has read the flags before
-// anything walks it.  Without the outputs (key null) it validates only.
+// the positions kept for the multipoles, one pass.  `bad` (device memory) gets
+// the build's number `id` when anything is rejected: the pair count then looks at
+// no candidate, so that a refusal does not wait for a search (rejected positions go
+// to cell 0).  Without the outputs (key null) it validates only.
 __device__ __forceinline__ void raise_flag(int* f) {
   __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -85,18 +86,17 @@ static __global__ void k_ingest(const double* __restrict__ x, const double* __re
                                 const double* __restrict__ z, const float* __restrict__ w, int64_t n, double L,
                                 double side, int nc, int32_t* __restrict__ key, int32_t* __restrict__ idx,
                                 double* __restrict__ kx, double* __restrict__ ky, double* __restrict__ kz,
-                                int* err) {
+                                int* err, int32_t* bad, int32_t id) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double a = x[i], b = y[i], c = z[i];
   const bool finite = isfinite(a) && isfinite(b) && isfinite(c);
   const bool ok = finite && a >= 0.0 && a < L && b >= 0.0 && b < L && c >= 0.0 && c < L;
+  const bool ok_w = !w || (isfinite(w[i]) && !(w[i] < 0.0f));
   if (!ok) raise_flag(err + (finite ? 1 : 0));
-  if (w) {
-    const float v = w[i];
-    if (!isfinite(v) || v < 0.0f) raise_flag(err + 2);
-  }
+  if (!ok_w) raise_flag(err + 2);
   if (!key) return;
+  if (!ok || !ok_w) *bad = id;
   const int cx = ok ? min((int)(a / side), nc - 1) : 0;
   const int cy = ok ? min((int)(b / side), nc - 1) : 0;
   const int cz = ok ? min((int)(c / side), nc - 1) : 0;
@@ -153,8 +153,10 @@ k_pairs(PairCfg c, const double* __restrict__ px, const double* __restrict__ py,
         const double* __restrict__ pz, const int32_t* __restrict__ perm,
         const int32_t* __restrict__ cell_of, const int32_t* __restrict__ cell_start, int64_t n,
         int64_t* __restrict__ cnt_off, int32_t* __restrict__ skey, int32_t* __restrict__ oi,
-        int32_t* __restrict__ oj, int32_t* __restrict__ place) {
+        int32_t* __restrict__ oj, int32_t* __restrict__ place, const int32_t* __restrict__ bad = nullptr,
+        int32_t id = 0) {
 #pragma clang fp contract(off)
+  const bool rejected = !EMIT && *bad == id;
   const int lane = (int)(threadIdx.x & 63);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const int64_t NN = (int64_t)c.N * c.N;
@@ -187,7 +189,7 @@ k_pairs(PairCfg c, const double* __restrict__ px, const double* __restrict__ py,
       if (lane >= d) inc += u;
     }
     const int pre = inc - cn;
-    const int total = __shfl(inc, 26, 64);
+    const int total = rejected ? 0 : __shfl(inc, 26, 64);
     const double ax = px[p], ay = py[p], az = pz[p];
     const int ia = EMIT ? perm[p] : 0;
     int64_t w = EMIT ? cnt_off[p] : 0;

@@ -76,3 +76,30 @@ def test_page_locked_host_memory_can_be_missing(workspace, monkeypatch):
     P, _ = plan.pairs_build(x, y, z)
     assert P > 0
     plan.close()
+
+
+def test_refusal_does_not_wait_for_the_search():
+    """1.5e5 galaxies in one cell (too many pairs, found by a search of 1.1e10
+    candidates): with one bad weight the catalogue is refused as wrong, and in less
+    than a quarter of the time of the search."""
+    import time
+
+    from paper_1705_03464_amd import Plan
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = get_config("cfg4tiny")
+    n = 150000
+    x = [_dev(40.0 + np.random.default_rng(k).random(n)) for k in range(3)]
+    w = torch.ones(n, dtype=torch.float32, device="cuda")
+    plan = Plan.from_workload(wl, precision="fp32")
+    took = {}
+    for _ in range(3):  # the first of each also allocates
+        for bad in (False, True):
+            w[n // 3] = -1.0 if bad else 1.0
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            assert _code(plan, *x, w=w) == (1 if bad else 4)
+            took[bad] = time.perf_counter() - t
+    print(f"search {took[False] * 1e3:.2f} ms, refusal {took[True] * 1e3:.2f} ms", flush=True)
+    assert took[True] < 0.25 * took[False]
+    plan.close()

@@ -99,9 +99,9 @@ typedef enum { PGX_ASSIGN_CIC = 0, PGX_ASSIGN_TSC = 1 } pgx_assignment;
  *   precision FP64_PLAIN: one field at a time in FP64 (transforms, sums).
  *             FP32_BATCHED: fields paired into complex grids, FP32 transforms
  *             and products, FP64 bin sums, normalisations and ratios.  At
- *             N = 64 the line transforms and the scatters' sums of the
- *             per-field transforms run in FP64 between grids stored in FP32;
- *             larger grids get no such help.
+ *             N = 64 the line transforms and the galaxy and pair-field
+ *             scatters' sums run in FP64 between grids stored in FP32; larger
+ *             grids get no such help.
  *   qeff_mode NOTSQ (default, equation Qeff_notsq with xi(d_w) := xi_gg(b)),
  *             SQUEEZED (equation Qeff), CONST_XIW (Qeff_notsq with xi(d_w) =
  *             xi_w_const, the paper's weighting-function table value).

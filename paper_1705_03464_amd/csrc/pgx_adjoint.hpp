@@ -562,7 +562,8 @@ struct GalaxyTable {
 // block takes kPairGradRounds x 256 consecutive pairs and sums them per galaxy
 // in LDS first, as the pairs of neighbouring lines are of the same few galaxies;
 // run sums before it only cost time (5.1 ms against 4.2).  At 3.6e8 pairs of 2e6
-// galaxies 9.0 -> 4.0 ms (12 KB of table and 8 rounds; 4.3 with 6 KB and 4 rounds
+// galaxies 9.0 -> 4.0 ms, with 4.9e7 atomics for 7.3e8 additions (waves wait for
+// 84% of their cycles; 12 KB of table and 8 rounds; 4.3 with 6 KB and 4 rounds
 // or 16 rounds, 8.7 with 48 KB: too few blocks per unit).  It is used from 24
 // pairs per galaxy on, where clustered candidates cross over, without and with it
 // (us): 13 pairs per galaxy 138 and 157, 21 203 and 206, 25 1783 and 1363 (5.0e7

@@ -140,12 +140,14 @@ k_zconv(const C<T>* __restrict__ ky_in, int64_t ky_slot, int n_slots, int pwz,
 
 // Points of the line a lane group gathers on in a z sweep: one lane's first
 // point (its k-th for k = s + t) is loaded a row ahead, and the line's bounds two
-// rows ahead.  Loads return in order, so a load of this row's bounds and points
-// that starts after the next row's elements waits for them and then twice more;
-// loaded ahead, a row costs one memory latency instead of three: 3.54 -> 3.32 ms
-// per launch at 512^3 (10 slots, 2.4 ms of bytes), 0.52 -> 0.46 at 256^3, the TSC
-// sweep at 256^3 0.78 -> 0.68.  A second row of elements in flight on top gave
-// 2% at 512^3 and cost the TSC sweep 25% (registers).
+// rows ahead.  Loads return in order: a load of this row's bounds that starts
+// behind the next row's elements waits for them, and its points for the bounds.
+// Ahead of them: 3.54 -> 3.32 ms per launch at 512^3 (10 slots, 2.4 ms of bytes),
+// 0.52 -> 0.46 at 256^3, the TSC sweep at 256^3 0.78 -> 0.68.  What is left is
+// mostly the transforms: by the counters the VALUs are busy 65% of the time and
+// waves wait on memory or LDS for 31% of their cycles (TSC at 256^3: 74%, 18%).  A
+// second row of elements in flight on top gave 2% at 512^3 and cost the TSC sweep
+// 25% (registers).
 template <typename T> struct SweepPoint {
   int x0;
   T fx, fy, fz;
@@ -571,7 +573,9 @@ __device__ __forceinline__ T pick3(const T* w, int j) {
 // yl[h P + p] (line-major pair index p).
 //
 // What bounds it: the points of the few crowded lines of a clustered
-// catalogue, a chain of loads and LDS atomics, not the dense output.  So all
+// catalogue, a chain of loads, run sums and LDS atomics, not the dense output (at
+// 512^3 the VALUs are busy 65% of the time, waves wait for 48% of their cycles; TSC
+// at 256^3: 45%, 31%, with 9 waves per unit).  So all
 // points of a wavefront's lines form one index range that its lanes walk
 // together (PointRanges), whatever line they belong to, or the whole block
 // where one wavefront has most of them (scatter_together): with TPL threads per

@@ -163,8 +163,9 @@ __device__ __forceinline__ int lpad(int i) { return i + (i >> kPadShift); }
 // candidate set (xi up to 4.4, most of it near 1e-3) sit at the edge of what FP32
 // grids hold: rounding inside the transforms decided whether they met one FP32
 // unit of the largest value (0.5 to 1.3 of it, by the order of the additions
-// alone).  The passes of a 64^3 grid are bound by their launches, so this costs
-// a few per cent there; larger grids would pay with half their occupancy.
+// alone).  The passes of a 64^3 grid, the smallest, are bound by their launches, so
+// this costs a few per cent there; larger grids would pay with half their
+// occupancy.
 template <typename T, int N> __host__ __device__ constexpr bool fft64() { return sizeof(T) == 4 && N <= 64; }
 // LDS entries (of type C<T>) of one line: those transformed in FP64 have room for
 // C<double>

@@ -14,7 +14,6 @@
 
 namespace pgx {
 
-
 // ----------------------------------------------------------------------------
 // Point sets: points sorted by (set, base line), where the base line of a point
 // is z0*N + y0 of its lower CIC corner.  line_start[set*N*N + l] is the first
@@ -284,7 +283,10 @@ template <typename T, bool TSC> __device__ __forceinline__ T source_weight(T w, 
 // wavefront first sums the contributions of adjacent points on the same x
 // node (clustered catalogues put many points on one node, and same-address
 // LDS atomics serialise), and only the last point of each run adds to the
-// line.  The next trip's points are in flight during the current one.
+// line.  The next trip's points are in flight during the current one.  With 3.6e8
+// HOD pairs at 512^3 the run sums fill the VALUs (busy all the time by the
+// counters; 3.8 ms per launch); with few points per line it is the transform and
+// its stores.
 // 64^3 lines hold FP64 (fft64): there the additions are FP64 ones, each point's
 // own (47 us per forward of the candidate set with run sums, 38 without).
 // ----------------------------------------------------------------------------

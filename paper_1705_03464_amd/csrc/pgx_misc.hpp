@@ -1,10 +1,9 @@
 // Smaller kernels: weights, deterministic FP64 reductions, the finalisation
 // formulas, and the pieces of the plain one-field-at-a-time path.
 #pragma once
-#include "pgx_pairs.hpp"
-
 #include "pgx_host.hpp"
 #include "pgx_kernels.hpp"
+#include "pgx_pairs.hpp"
 
 namespace pgx {
 

@@ -139,10 +139,11 @@ __device__ __forceinline__ int wrap_cell(int c, int nc) { return c < 0 ? c + nc 
 // and the place itself (the value the sort carries along) only; the midpoint's
 // CIC corner and fractions are recomputed after the sort by k_pair_cic, with
 // coalesced stores.
-// Bound by instruction issue (a step of 64 candidates is a cell search, four
-// loads and the FP64 test): the orientation is looked at for kept pairs only, the
-// periodic fold only where a neighbour cell lies across the box, and the cell is
-// wave-uniform.  Counting and emission of 3.6e8 pairs 5.3 + 6.3 -> 4.5 + 5.8 ms, of
+// Bound by its instructions (a step of 64 candidates is a cell search, four loads
+// and the FP64 test): by the counters the VALUs are busy 56 to 69% of the time,
+// and waves wait on memory or LDS for 10% of their cycles.  So the orientation is
+// looked at for kept pairs only, the periodic fold only where a neighbour cell
+// lies across the box, and the cell is wave-uniform.  Counting and emission of 3.6e8 pairs 5.3 + 6.3 -> 4.5 + 5.8 ms, of
 // 3.4e6 pairs of 5e5 galaxies 0.57 + 0.63 -> 0.52 + 0.59 ms.  Leaving out cells
 // beyond the largest separation's reach gave 7% on the first and cost 7% on the
 // second (its test per cell against one step of candidates).

@@ -1,6 +1,8 @@
 """CPU model of the device's FP32 transform chain (test infrastructure).
 
-The device transforms each grid line with a Stockham schedule: radix-8
+With FP32 arithmetic it is the chain of 128^3 and larger grids; 64-point lines run
+on the device with FP64 arithmetic, twiddles and exchange and FP32 storage.  The
+device transforms each grid line with a Stockham schedule: radix-8
 stages (64 = 8 x 8, 512 = 8 x 8 x 8), each a twiddle multiplication by the
 FP64-computed, rounded stage twiddles and an in-register DFT built from
 radix-4 butterflies and constant rotations; stages exchange the line through

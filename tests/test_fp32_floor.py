@@ -8,7 +8,8 @@ FP32 unit of the largest value.  A model of the device's transform schedule
 (tests/fp32_model.py: the same radix-8 stages, rotations, stage twiddles,
 LDS exchanges and FP32 storage between passes) shows:
   * in FP32 arithmetic it misses that bar by a factor of 1.5 - 3 on this
-    catalogue, as the device kernels do (by up to 2.6);
+    catalogue, as device kernels with FP32 arithmetic in 64-point lines did (by
+    up to 2.6; they run them in FP64 since, the next item);
   * with FP64 arithmetic in every pass but the grids still stored in FP32
     between passes, the rounding of the stored values alone takes 0.3 - 0.9
     of the bar: no single-precision storage of the spectra holds it with a

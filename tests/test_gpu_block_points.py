@@ -1,6 +1,7 @@
-"""The x-pass scatters and gathers take the points of a block's lines as one
-index range walked by all its threads.  Their edges: more points on one line
-than the block keeps in registers, lines and whole blocks without points, and
+"""The x-pass scatters take the points of a wavefront's lines, the gathers those
+of a block's, as one index range walked by all its threads.  Their edges: more
+points on one line than the block keeps in registers, lines and whole blocks
+without points, and
 a task list that does not fill its last block; at every number of threads per
 line below a wavefront (64^3, 128^3, 256^3), CIC and TSC, per-field transforms
 and dual form, against the oracle.

@@ -333,8 +333,8 @@ def _crowded_case():
 def test_512_crowded_nodes(algo):
     """HOD candidates (50 per halo, NFW profiles) at 512^3 in a 250 Mpc/h box:
     up to ~2500 pair midpoints and ~40 galaxies share one grid node, so the
-    scatters' wavefront run sums (active when a line is a whole wavefront, as
-    at this grid) merge long runs.  Weighted; counts bit-exact, xi_gg and the
+    scatters' wavefront run sums (a line is a whole wavefront at this grid)
+    merge long runs.  Weighted; counts bit-exact, xi_gg and the
     smallest- and largest-separation fields against the oracle for the
     per-field transforms and both dual-form variants."""
     wl, cat, w, pairs, fields, ref = _crowded_case()

@@ -19,8 +19,10 @@ namespace pgx {
 // when it leaves a range.  Combined indices have 64 bits: a point counts once
 // for every line of the group that it reaches (up to 16 of a block's lines with
 // TSC), so a catalogue below 2^31 points, which point indices fit, can have 2^35
-// of them.  (32-bit ones are no faster: 512^3 step 27.8 ms, here 27.6; the TSC fit
-// at 256^3 4.49 and 4.49.)
+// of them.  (Against 32-bit ones, which wrap there, the scatters take up to 2.4%
+// longer: 504 and 515 us at 256^3, 7.45 and 7.51 ms with 3.6e8 HOD pairs; whole
+// passes up to 0.4%.  A walk by steps with the point and the rest of its range in
+// 32 bits took 8.4 ms there.)
 template <int NR, int NT> struct PointRanges {
   int64_t off[NR];     // combined index of the range's first point
   uint32_t first[NR];  // its first point minus that, modulo 2^32
